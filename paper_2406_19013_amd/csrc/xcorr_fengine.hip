@@ -3,9 +3,10 @@
 // 1024 channels -> per-(input, channel) EQ gain -> 4+4-bit requantisation ->
 // corner turn into the X-engine's [T][F][N] order.
 //
-// Persistent work-groups of 8 waves (two per SIMD); an item is one spectrum
-// m of 16 inputs, 2 per wave, each filtered and transformed by one wave.  Per
-// input and spectrum:
+// Persistent work-groups of 8 waves (two per SIMD); an item is one spectrum,
+// or two consecutive ones, of 16 inputs, 2 per wave.  A wave filters and
+// transforms an input's one or two spectra in lockstep.  Per input and
+// spectrum:
 //   y[q] = sum_k h[k P + q] x[(m + k) P + q]            q < P = 2048
 //   z[n] = y[2n] + i y[2n + 1]                          n < 1024
 //   Z    = 1024-point complex DFT of z (radix 16 x 16 x 4)
@@ -14,14 +15,25 @@
 // A lane reads 32 consecutive samples of each tap with 16-byte loads (one
 // input ahead of the one it transforms); the prototype is copied into LDS
 // once per work-group, ordered so that the 128 coefficients of a lane's sample
-// positions come as 32 conflict-free 16-byte reads per transform (held in
-// registers they took 512 per lane and left room for one wave per SIMD);
-// four LDS exchanges per transform (into the stride-64 order, between
-// the three radix passes, and for the Z[N - c] pairs).  Twiddles are built
+// positions come as 32 conflict-free 16-byte reads (held in registers they
+// took 512 per lane and left room for one wave per SIMD); three full LDS
+// exchanges per transform (into the stride-64 order and between the three
+// radix passes) and half of one for the Z[N - c] pairs.  Twiddles are built
 // per lane from one base value by short power products (at most three
 // roundings deep).  The 16 inputs' codes are gathered in LDS and leave as one
 // 16-byte row per (spectrum, channel).  Arithmetic in fp32; rounding is
 // round-half-to-even.
+//
+// What bounds it: vector arithmetic (79 % of the cycles issue it), then the
+// LDS exchanges.  Two spectra at once share the coefficient reads, three of
+// every four sample conversions' blocks, the twiddle powers and the gains:
+// 1,136 vector instructions per transform instead of 1,600.  192 inputs x
+// 4096 spectra: 2.84 ms with one spectrum at a time; 2.37 ms with two, no
+// waits inside an exchange (a wave's LDS accesses execute in order) and pairs
+// Y[c], Y[N - c] formed together; 2.10 ms with exchange layouts free of bank
+// conflicts; 1.94 ms with 16-byte exchange reads (LDS busy 57 -> 43 % of the
+// cycles).  The rounding of every step is as in the one-spectrum kernel, so the
+// codes are the same bytes.
 #include "xcorr.h"
 #include "xcorr_internal.h"
 
@@ -43,8 +55,7 @@ constexpr int kFeWaves = 8;
 constexpr int kFeThreads = 64 * kFeWaves;
 constexpr int kFeInputsPerWave = kFeGroup / kFeWaves;
 constexpr int kFeWgsPerCu = 1;   // 8 waves: two per SIMD, up to 256 registers each
-constexpr int kFeBufStride = 17;                    // float2 per row of the pass exchanges (16 + 1 pad)
-constexpr int kFeBufFloats = 2 * 64 * kFeBufStride;  // per wave: 64 rows
+constexpr int kFeBufFloats = 2 * 1088;              // per wave: the widest exchange (32 rows of 34 float2)
 constexpr int kFeCodeStride = 20;                   // bytes per channel row of the code tile (16 + pad)
 constexpr int kFeSmemProto = kFeTaps * kFeP * 4;    // the prototype, 32 KB
 
@@ -107,31 +118,53 @@ __device__ constexpr Table<64> kW2048 = make_powers<64>(2048);   // real-unpack 
 constexpr Table<16> kW32 = make_powers<16>(32);                  // W2048^(64 v) = W32^v
 
 // ---- complex helpers ----------------------------------------------------------
+//
+// The rounding of every product is written out (which of the two products of
+// a complex multiplication is fused): a code may sit on a rounding boundary of
+// the requantiser, and the same bytes must come out whatever the compiler
+// would contract, in the one- and the two-spectrum kernel alike.
+#pragma clang fp contract(off)
 
 struct cf {
     float r, i;
 };
 __device__ __forceinline__ cf cadd(cf a, cf b) { return {a.r + b.r, a.i + b.i}; }
 __device__ __forceinline__ cf csub(cf a, cf b) { return {a.r - b.r, a.i - b.i}; }
-__device__ __forceinline__ cf cmul(cf a, cf b) { return {a.r * b.r - a.i * b.i, a.r * b.i + a.i * b.r}; }
 __device__ __forceinline__ cf cmul_mi(cf a) { return {a.i, -a.r}; }   // a * (-i)
+// a b, the imaginary part fused on a.r b.i (cmul_f) or on a.i b.r (cmul_g)
+__device__ __forceinline__ cf cmul_f(cf a, cf b)
+{
+    return {fmaf(a.r, b.r, -(a.i * b.i)), fmaf(a.r, b.i, a.i * b.r)};
+}
+__device__ __forceinline__ cf cmul_g(cf a, cf b)
+{
+    return {fmaf(a.r, b.r, -(a.i * b.i)), fmaf(a.i, b.r, a.r * b.i)};
+}
 
 // p[k] = w^k for k < 16: w, w^2, w^3 and w^4, w^8, w^12, then products
 // (each power at most three roundings from w)
 __device__ __forceinline__ void powers16(cf w, cf (&p)[16])
 {
+    auto square = [](cf a) { return cf{fmaf(a.r, a.r, -(a.i * a.i)), a.r * a.i + a.r * a.i}; };
     p[0] = cf{1.f, 0.f};
     p[1] = w;
-    p[2] = cmul(w, w);
-    p[3] = cmul(p[2], w);
-    p[4] = cmul(p[2], p[2]);
-    p[8] = cmul(p[4], p[4]);
-    p[12] = cmul(p[8], p[4]);
+    p[2] = square(w);
+    p[3] = cmul_f(p[2], w);
+    p[4] = square(p[2]);
+    p[8] = square(p[4]);
+    p[12] = cmul_f(p[8], p[4]);
 #pragma unroll
     for (int a = 4; a < 16; a += 4)
 #pragma unroll
         for (int b = 1; b < 4; ++b)
-            p[a + b] = cmul(p[a], p[b]);
+            p[a + b] = cmul_g(p[a], p[b]);
+}
+// z times its twiddle w^k
+__device__ __forceinline__ cf twiddle(cf z, const cf (&p)[16], int k)
+{
+    if (k == 0)
+        return {fmaf(z.i, -0.f, z.r), fmaf(z.r, 0.f, z.i)};
+    return k == 8 ? cmul_f(z, p[k]) : cmul_g(z, p[k]);
 }
 
 // forward 4-point DFT in place: x[k] = sum_n x[n] (-i)^{nk}
@@ -148,23 +181,27 @@ __device__ __forceinline__ void dft4(cf &x0, cf &x1, cf &x2, cf &x3)
 // output is in natural order
 __device__ __forceinline__ void dft16(cf *x)
 {
-    // n = 4a + b: 4-point DFTs over a for each b -> U[b][c] (stored at x[4c + b]... )
+    // n = 4a + b: 4-point DFTs over a for each b -> U[b][c] at x[4c + b]
+#pragma unroll
     for (int b = 0; b < 4; ++b)
-        dft4(x[b], x[4 + b], x[8 + b], x[12 + b]);   // x[4c + b] = U[b][c]
-    // twiddles W16^{b c}
+        dft4(x[b], x[4 + b], x[8 + b], x[12 + b]);
+    // twiddles W16^{b c} = exp(-2 pi i b c / 16); x * (re, im) with the fused
+    // product the one of x.i (mul_i) or of x.r (mul_r)
     constexpr float c1 = 0.92387953251128674f, s1 = 0.38268343236508978f, r2 = 0.70710678118654752f;
-    // (b, c) -> W16^{bc} = exp(-2 pi i b c / 16)
-    x[4 * 1 + 1] = cmul(x[5], cf{c1, -s1});
-    x[4 * 2 + 1] = cmul(x[9], cf{r2, -r2});
-    x[4 * 3 + 1] = cmul(x[13], cf{s1, -c1});
-    x[4 * 1 + 2] = cmul(x[6], cf{r2, -r2});
-    x[4 * 2 + 2] = cmul_mi(x[10]);
-    x[4 * 3 + 2] = cmul(x[14], cf{-r2, -r2});
-    x[4 * 1 + 3] = cmul(x[7], cf{s1, -c1});
-    x[4 * 2 + 3] = cmul(x[11], cf{-r2, -r2});
-    x[4 * 3 + 3] = cmul(x[15], cf{-c1, s1});
+    auto mul_i = [](cf a, float re, float im) { return cf{fmaf(a.i, -im, re * a.r), fmaf(a.i, re, im * a.r)}; };
+    auto mul_r = [](cf a, float re, float im) { return cf{fmaf(a.r, re, -(im * a.i)), fmaf(a.r, im, re * a.i)}; };
+    x[5] = mul_i(x[5], c1, -s1);
+    x[9] = mul_i(x[9], r2, -r2);
+    x[13] = mul_i(x[13], s1, -c1);
+    x[6] = mul_i(x[6], r2, -r2);
+    x[10] = cmul_mi(x[10]);
+    x[14] = mul_i(x[14], -r2, -r2);
+    x[7] = mul_i(x[7], s1, -c1);
+    x[11] = mul_r(x[11], -r2, -r2);
+    x[15] = mul_r(x[15], -c1, s1);
     // 4-point DFTs over b for each c: X[c + 4 d] from x[4c + b]
     cf y[16];
+#pragma unroll
     for (int c = 0; c < 4; ++c) {
         cf a0 = x[4 * c], a1 = x[4 * c + 1], a2 = x[4 * c + 2], a3 = x[4 * c + 3];
         dft4(a0, a1, a2, a3);
@@ -173,19 +210,46 @@ __device__ __forceinline__ void dft16(cf *x)
         y[c + 8] = a2;
         y[c + 12] = a3;
     }
+#pragma unroll
     for (int k = 0; k < 16; ++k)
         x[k] = y[k];
 }
 
-// this wave's LDS writes done before any lane reads them (and its reads done
-// before the buffer is written again); the memory clobber keeps the compiler
-// from moving LDS accesses across
-__device__ __forceinline__ void lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-__device__ __forceinline__ int quant4(float v)
+// W2048^(lane + 64 v) = W2048^lane W32^v, with the roundings of the
+// per-lane products the unpack step was first written with
+__device__ __forceinline__ cf unpack_twiddle(cf wl, int v)
 {
-    const float r = __builtin_rintf(v);   // round half to even
-    return (int)fminf(fmaxf(r, -8.0f), 7.0f);
+    if (v == 0)
+        return wl;
+    const cf k{kW32.re[v], kW32.im[v]};
+    const bool alt = v >= 9 && v <= 11;
+    const float r = alt ? fmaf(wl.i, -k.i, k.r * wl.r) : fmaf(wl.r, k.r, -(wl.i * k.i));
+    const float i = v >= 9 && v <= 12 ? fmaf(wl.r, k.i, wl.i * k.r) : fmaf(wl.i, k.r, wl.r * k.i);
+    return {r, i};
+}
+
+// A wave's LDS accesses are executed in order, so an exchange between its
+// lanes needs no wait between the writes and the reads (nor before the next
+// exchange overwrites the buffer): the fence only keeps the compiler from
+// moving accesses across it.
+__device__ __forceinline__ void wave_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// work-group barrier that waits for this wave's LDS accesses only (the loads
+// of the next samples and the stores of the codes stay in flight)
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// The packed code of one channel: re and im scaled, clipped to [-8, 7] and
+// rounded half to even (clipping first gives the same: the bounds are whole).
+// Adding 1.5 2^23 rounds to a whole number whose low bits are the sum's.
+__device__ __forceinline__ uint32_t pack_code(float g, cf y)
+{
+    constexpr float kRound = 12582912.0f;
+    const float re = fminf(fmaxf(g * y.r, -8.0f), 7.0f) + kRound;
+    const float im = fminf(fmaxf(g * y.i, -8.0f), 7.0f) + kRound;
+    return (__builtin_bit_cast(uint32_t, re) << 4) | (__builtin_bit_cast(uint32_t, im) & 15u);
 }
 
 struct FeArgs {
@@ -194,24 +258,29 @@ struct FeArgs {
     int N;
     const float *h;       // [taps * P]
     const float *gains;   // [N][1024]
-    int64_t n_spectra;
+    int n_spectra;
     void *out;            // CODES: uint8 [n_spectra][1024][N]; else float2 [N][n_spectra][1024]
 };
 
-// Raw samples of one (input, spectrum) for this lane: 32 consecutive
-// samples x[(m + k) P + 32 lane + t] of each tap k, as two 16-byte loads.
+// Raw samples for NS consecutive spectra from m: this lane's 32 consecutive
+// samples of the blocks m .. m + NS + 2 (2048 samples each) as two 16-byte
+// loads a block; blocks past the last spectrum's are that spectrum's again.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+template <int NS>
 struct FeRaw {
-    u32x4 v[kFeTaps][2];
+    u32x4 v[kFeTaps + NS - 1][2];
 };
-__device__ __forceinline__ void fe_load(const FeArgs &a, int input, int64_t m, FeRaw &r)
+template <int NS>
+__device__ __forceinline__ void fe_load(const FeArgs &a, int input, int m, FeRaw<NS> &r)
 {
     const int lane = threadIdx.x & 63;
-    const u32x4 *x = (const u32x4 *)(a.adc + (int64_t)input * a.S + m * kFeP + 32 * lane);
+    const u32x4 *x = (const u32x4 *)(a.adc + (int64_t)input * a.S + (int64_t)m * kFeP + 32 * lane);
+    const int last = a.n_spectra - 1 - m + kFeTaps - 1;   // last block a spectrum needs
 #pragma unroll
-    for (int k = 0; k < kFeTaps; ++k) {
-        r.v[k][0] = __builtin_nontemporal_load(x + k * (kFeP / 16));
-        r.v[k][1] = __builtin_nontemporal_load(x + k * (kFeP / 16) + 1);
+    for (int k = 0; k < kFeTaps + NS - 1; ++k) {
+        const int b = k < kFeTaps ? k : min(k, last);
+        r.v[k][0] = x[b * (kFeP / 16)];
+        r.v[k][1] = x[b * (kFeP / 16) + 1];
     }
 }
 
@@ -221,19 +290,15 @@ __device__ __forceinline__ float byte_at(const u32x4 &v, int t)
     return (float)(int8_t)(w >> (8 * (t & 3)));
 }
 
-// One wave's transform of one (input, spectrum), in two parts: the FIR of
-// its raw samples (after which the raw registers take the next input's
-// loads), then the FFT, which returns the 16 channel values c = lane + 64 v
-// (v < 16) of the real spectrum in y[v].
-// hl: the prototype in LDS, float4 (k, t4, lane) = h[k P + 32 lane + 4 t4 ..].
-struct FeBases {
-    cf w1024, w64, w2048;   // W1024^lane, W64^(lane % 4), W2048^lane
-};
-__device__ __forceinline__ void fe_fir(const FeRaw &raw, const float4 *hl, cf (&z)[16])
+// FIR of this lane's 32 samples of NS consecutive spectra -> z[s][j] for
+// n = 16 lane + j; samples 4 t4 .. 4 t4 + 3 make z[2 t4] and z[2 t4 + 1].
+// hl: the prototype in LDS, float4 (k, t4, lane) = h[k P + 32 lane + 4 t4 ..];
+// each coefficient read and each converted sample serves every spectrum that
+// uses it.
+template <int NS>
+__device__ __forceinline__ void fe_fir(const FeRaw<NS> &raw, const float4 *hl, cf (&z)[NS][16])
 {
     const int lane = threadIdx.x & 63;
-    // FIR on this lane's 32 samples -> z[n] for n = 16 lane + j; samples
-    // 4 t4 .. 4 t4 + 3 make z[2 t4] and z[2 t4 + 1]
 #pragma unroll
     for (int t4 = 0; t4 < 8; ++t4) {
         // The coefficient reads are the same for every transform: left alone
@@ -242,235 +307,341 @@ __device__ __forceinline__ void fe_fir(const FeRaw &raw, const float4 *hl, cf (&
         // of four between its neighbours.
         int l = lane;
         asm volatile("" : "+v"(l) : : "memory");
-        float r0 = 0.f, i0 = 0.f, r1 = 0.f, i1 = 0.f;
+        float4 h[kFeTaps];
 #pragma unroll
-        for (int k = 0; k < kFeTaps; ++k) {
-            const float4 h = hl[(k * 8 + t4) * 64 + l];
-            const u32x4 &v = raw.v[k][t4 >> 2];
+        for (int k = 0; k < kFeTaps; ++k)
+            h[k] = hl[(k * 8 + t4) * 64 + l];
+        float4 y[NS];
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            y[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int b = 0; b < kFeTaps + NS - 1; ++b) {
+            const u32x4 &v = raw.v[b][t4 >> 2];
             const int t = (4 * t4) & 15;
-            r0 = fmaf(h.x, byte_at(v, t), r0);
-            i0 = fmaf(h.y, byte_at(v, t + 1), i0);
-            r1 = fmaf(h.z, byte_at(v, t + 2), r1);
-            i1 = fmaf(h.w, byte_at(v, t + 3), i1);
+            const float x0 = byte_at(v, t), x1 = byte_at(v, t + 1), x2 = byte_at(v, t + 2), x3 = byte_at(v, t + 3);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int k = b - s;
+                if (k >= 0 && k < kFeTaps) {
+                    y[s].x = fmaf(h[k].x, x0, y[s].x);
+                    y[s].y = fmaf(h[k].y, x1, y[s].y);
+                    y[s].z = fmaf(h[k].z, x2, y[s].z);
+                    y[s].w = fmaf(h[k].w, x3, y[s].w);
+                }
+            }
         }
-        z[2 * t4] = cf{r0, i0};
-        z[2 * t4 + 1] = cf{r1, i1};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            z[s][2 * t4] = cf{y[s].x, y[s].y};
+            z[s][2 * t4 + 1] = cf{y[s].z, y[s].w};
+        }
     }
 }
 
-__device__ __forceinline__ void fe_fft(cf (&z)[16], const FeBases &bs, float *buf, cf (&y)[16])
+struct FeBases {
+    cf w1024, w64;   // W1024^lane, W64^(lane / 16)
+};
+
+// The FFT of NS spectra of one input by one wave, in lockstep (the twiddles
+// are formed once, and one spectrum's exchange runs under the other's
+// arithmetic); halfway() is called between the passes, then emit(s, v, second, y) for the channels c = lane + 64 v,
+// v < 8 (second = false), and their partners 1024 - c (second = true); lane
+// 0's partner for v = 0 is channel 512.
+// buf: this wave's exchange buffer; wt: the unpack twiddles (see kFeWtEntries).
+// The layouts give 16-byte reads (measured 5.7 cycles for 64 lanes, against 8
+// to 16 for the ds_read2_b64 that pairs of 8-byte reads become) and writes
+// whose 16 lanes at a time fall on distinct bank pairs.
+template <int NS, class Halfway, class Emit>
+__device__ __forceinline__ void fe_fft(cf (&z)[NS][16], const FeBases &bs, float2 *buf, const float2 *wt,
+                                       Halfway &&halfway, Emit &&emit)
 {
     // the exchange addresses are the same for every transform; an opaque lane
-    // makes the compiler form them here instead of keeping about a hundred
-    // of them live across the loop (which spilled with two waves per SIMD)
+    // makes the compiler form them here instead of keeping them live across
+    // the loop
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));
-    // likewise the twiddles derived from the per-lane bases (about a hundred
-    // registers if kept across the loop): formed anew for each transform
+    // likewise the twiddles derived from the per-lane bases
     FeBases b = bs;
-    asm volatile("" : "+v"(b.w1024.r), "+v"(b.w1024.i), "+v"(b.w64.r), "+v"(b.w64.i), "+v"(b.w2048.r),
-                 "+v"(b.w2048.i));
-    // exchange 0: z at n + n / 16, read back with stride 64 (n = 64 n1 + lane)
+    asm volatile("" : "+v"(b.w1024.r), "+v"(b.w1024.i), "+v"(b.w64.r), "+v"(b.w64.i));
+    const int k1 = lane & 15, m2 = lane >> 4;   // passes 2 and 3 (m2 is r there)
+    // Exchanges 0 and 1 move a 64 x 16 matrix M[16 g + j][a] whose row
+    // a = 4.. has its g, j spread over lanes: written by lane 4 a + g (element
+    // j at 2 (16 g + j) + a % 2, padded), read by lane 16 g + j, two values of
+    // a to a 16-byte read.
+    float2 *const w0 = buf + 34 * (lane & 3) + ((lane >> 2) & 1) + 136 * (lane >> 3);
+    const float4 *const r0 = (const float4 *)(buf + 2 * lane + 2 * (lane >> 4));
+    // exchange 0: lane l holds z[16 l + j]; lane l takes z[64 n1 + l]
 #pragma unroll
-    for (int j = 0; j < 16; ++j)
-        *(float2 *)&buf[2 * (17 * lane + j)] = make_float2(z[j].r, z[j].i);
-    lds_sync();
+    for (int s = 0; s < NS; ++s) {
 #pragma unroll
-    for (int n1 = 0; n1 < 16; ++n1) {
-        const float2 v = *(const float2 *)&buf[2 * (68 * n1 + lane + (lane >> 4))];
-        z[n1] = cf{v.x, v.y};
+        for (int j = 0; j < 16; ++j)
+            w0[2 * j] = make_float2(z[s][j].r, z[s][j].i);
+        wave_order();
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            const float4 v = r0[68 * n];
+            z[s][2 * n] = cf{v.x, v.y};
+            z[s][2 * n + 1] = cf{v.z, v.w};
+        }
+        wave_order();
     }
-    lds_sync();
-    // pass 1: 16-point DFT over n1 (n = 64 n1 + l), twiddle W1024^{l k1}
-    dft16(z);
-    {
+    // pass 1: 16-point DFT over n1 (n = 64 n1 + l), twiddle W1024^{l k1};
+    // lane l holds A[l][k1]
+    // pass 2: lane = (m2, k1); 16-point DFT over m1 of A[4 m1 + m2][k1], twiddle W64^{m2 j1};
+    // B[k1][m2][j1] at 2 (16 (j1 % 4) + k1) + m2 % 2, rows (m2 / 2, j1 / 4)
+    float2 *const w2 = buf + 2 * k1 + (m2 & 1) + 512 * (m2 >> 1);
+    const float4 *const r2 = (const float4 *)(buf + 2 * lane);
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
         cf tw[16];
-        powers16(b.w1024, tw);
 #pragma unroll
-        for (int k1 = 0; k1 < 16; ++k1) {
-            const cf v = cmul(z[k1], tw[k1]);
-            // A[n2 = lane][k1] at row n2, column k1
-            *(float2 *)&buf[2 * (lane * kFeBufStride + k1)] = make_float2(v.r, v.i);
+        for (int s = 0; s < NS; ++s) {
+            dft16(z[s]);
+            if (s == 0)
+                powers16(pass ? b.w64 : b.w1024, tw);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const cf v = twiddle(z[s][k], tw, k);
+                (pass ? w2[32 * (k & 3) + 128 * (k >> 2)] : w0[2 * k]) = make_float2(v.r, v.i);
+            }
+            wave_order();
+            // pass 3 takes j1 = r + 4 u, q = m2 of its k1, at 4 u + q
+#pragma unroll
+            for (int n = 0; n < 8; ++n) {
+                const float4 v = pass ? r2[64 * (n >> 1) + 256 * (n & 1)] : r0[68 * n];
+                z[s][2 * n] = cf{v.x, v.y};
+                z[s][2 * n + 1] = cf{v.z, v.w};
+            }
+            wave_order();
+        }
+        if (pass == 0)
+            halfway();
+    }
+    // pass 3: lane = (r, k1); for j1 = r + 4 u: 4-point DFT over q -> Z[k1 + 16 j1 + 256 j2],
+    // that is Z[lane + 64 v], v = u + 4 j2: every lane already holds its
+    // channels c = lane + 64 v; the partners 1024 - c = (64 - lane) + 64 (15 - v)
+    // of v < 8 come from lane 64 - lane
+    float2 *const lin = buf + lane;
+    const float2 *const rev = buf + 64 - lane;
+    const float4 *const wlin = (const float4 *)(wt + 2 * lane), *const wrev = (const float4 *)(wt + 128 - 2 * lane);
+    cf zn[NS][8];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            cf *q = &z[s][4 * u];   // Z[lane + 64 (u + 4 j2)] at 4 u + j2
+            dft4(q[0], q[1], q[2], q[3]);
+            lin[64 * u] = make_float2(q[2].r, q[2].i);
+            lin[64 * u + 256] = make_float2(q[3].r, q[3].i);
+        }
+        wave_order();
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            // (lane 0, v = 0 has no partner row: see below)
+            const float2 q = rev[v == 0 && lane == 0 ? 0 : 64 * (7 - v)];
+            zn[s][v] = cf{q.x, q.y};
+        }
+        wave_order();
+    }
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+        const float4 w4 = wlin[65 * (v >> 1)], x4 = wrev[65 * (7 - (v >> 1))];
+        const cf wa = v & 1 ? cf{w4.z, w4.w} : cf{w4.x, w4.y};
+        const cf wb = v & 1 ? cf{x4.x, x4.y} : cf{x4.z, x4.w};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            // Y[c] = (Z[c] + Z*[N - c]) / 2 - i W^c (Z[c] - Z*[N - c]) / 2
+            const cf p = z[s][4 * (v & 3) + (v >> 2)];
+            cf q = zn[s][v];
+            if (v == 0 && lane == 0)
+                q = p;   // channel 0 is its own partner
+            const float er = p.r + q.r, ei = p.i - q.i, dr = p.r - q.r, di = p.i + q.i;
+            {
+                const float odr = fmaf(wa.r, dr, -(wa.i * di));
+                const float odi = v == 0 ? fmaf(wa.r, di, wa.i * dr) : fmaf(wa.i, dr, wa.r * di);
+                emit(s, v, false, cf{0.5f * (er + odi), 0.5f * (ei - odr)});
+            }
+            // the partner's sums and differences are the same up to sign
+            // (channel 512 for lane 0, v = 0: its own partner)
+            float fr = er, fi = -ei, gr = -dr, gi = di;
+            if (v == 0 && lane == 0) {
+                const cf m = z[s][2];   // v = 8: u = 0, j2 = 2
+                fr = m.r + m.r;
+                fi = m.i - m.i;
+                gr = m.r - m.r;
+                gi = m.i + m.i;
+            }
+            const float odr = fmaf(wb.r, gr, -(wb.i * gi));
+            const float odi = fmaf(wb.i, gr, wb.r * gi);
+            emit(s, v, true, cf{0.5f * (fr + odi), 0.5f * (fi - odr)});
         }
     }
-    lds_sync();
-    // pass 2: lane = (k1, m2); 16-point DFT over m1 of A[4 m1 + m2][k1], twiddle W64^{m2 j1}
-    const int k1 = lane >> 2, m2 = lane & 3;
-#pragma unroll
-    for (int m1 = 0; m1 < 16; ++m1) {
-        const float2 v = *(const float2 *)&buf[2 * ((4 * m1 + m2) * kFeBufStride + k1)];
-        z[m1] = cf{v.x, v.y};
-    }
-    lds_sync();
-    dft16(z);
-    {
-        cf tw[16];
-        powers16(b.w64, tw);
-#pragma unroll
-        for (int j1 = 0; j1 < 16; ++j1)
-            z[j1] = cmul(z[j1], tw[j1]);
-    }
-    // exchange: B[k1][m2][j1] at row 4 k1 + m2 (17-float2 rows), column j1
-#pragma unroll
-    for (int j1 = 0; j1 < 16; ++j1)
-        *(float2 *)&buf[2 * ((4 * k1 + m2) * kFeBufStride + j1)] = make_float2(z[j1].r, z[j1].i);
-    lds_sync();
-    // pass 3: lane = (k1, r); for j1 = r + 4 u: 4-point DFT over m2 -> Z[k1 + 16 j1 + 256 j2]
-    const int r = lane & 3;
-    cf Z[16];   // Z[u][j2] at 4 u + j2
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int j1 = r + 4 * u;
-        cf b[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float2 v = *(const float2 *)&buf[2 * ((4 * k1 + q) * kFeBufStride + j1)];
-            b[q] = cf{v.x, v.y};
-        }
-        dft4(b[0], b[1], b[2], b[3]);
-#pragma unroll
-        for (int j2 = 0; j2 < 4; ++j2)
-            Z[4 * u + j2] = b[j2];
-    }
-    lds_sync();
-    // Z in natural order k = k1 + 16 (r + 4 u) + 256 j2, stored at k + k / 16
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int j2 = 0; j2 < 4; ++j2) {
-            const int k = k1 + 16 * (r + 4 * u) + 256 * j2;
-            *(float2 *)&buf[2 * (k + (k >> 4))] = make_float2(Z[4 * u + j2].r, Z[4 * u + j2].i);
-        }
-    lds_sync();
-    // real spectrum of channels c = lane + 64 v: W2048^c = W2048^lane W32^v
-    const cf wl = b.w2048;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int c = lane + 64 * v;
-        const int cn = (kFeN - c) & (kFeN - 1);
-        const float2 p = *(const float2 *)&buf[2 * (c + (c >> 4))];
-        const float2 q = *(const float2 *)&buf[2 * (cn + (cn >> 4))];
-        const cf zc{p.x, p.y}, zn{q.x, -q.y};   // Z[c], conj Z[N - c]
-        const cf e = cadd(zc, zn), d = csub(zc, zn);
-        const cf w = v ? cmul(wl, cf{kW32.re[v], kW32.im[v]}) : wl;
-        const cf od = cmul(w, d);                // W^c (Z[c] - Z*[N - c])
-        // Y = e / 2 - i od / 2
-        y[v] = cf{0.5f * (e.r + od.i), 0.5f * (e.i - od.r)};
-    }
-    lds_sync();
 }
 
-template <bool CODES>
+// LDS: the prototype, the table W2048^c, an exchange buffer per wave and
+// (CODES) a code tile per spectrum
+// W2048^(l + 64 v) at 2 l + v % 2 of row v / 2 (130 entries); the last two of
+// row p serve lane 0's partners: W2048^(64 (2 p + 1)), W2048^(64 (2 p + 2))
+// (p = 7: W2048^512)
+constexpr int kFeWtEntries = 8 * 130;
+constexpr int kFeSmemBase = kFeSmemProto + kFeWtEntries * 8 + kFeWaves * kFeBufFloats * 4;
+constexpr int fe_smem_bytes(bool codes, int ns) { return kFeSmemBase + (codes ? ns * kFeN * kFeCodeStride : 0); }
+
+template <bool CODES, int NS>
 __device__ __forceinline__ void fengine_body(uint8_t *smem, const FeArgs &a)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // items (spectrum m of input group g) in order m fastest; each XCD takes a
-    // contiguous run, so the taps shared by consecutive spectra meet in its L2
-    const int64_t groups = a.N / kFeGroup;
-    const int64_t items = a.n_spectra * groups;
-    const int64_t per_xcd = (items + 7) / 8;
-    const int64_t first = (int64_t)(blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    const int64_t end = min(items, (int64_t)((blockIdx.x & 7) + 1) * per_xcd);
-    const int64_t stride = gridDim.x >> 3;
+    // items (NS spectra of an input group g); each XCD takes a contiguous
+    // run, so the taps shared by consecutive spectra meet in its L2
+    const unsigned groups = a.N / kFeGroup, runs = (a.n_spectra + NS - 1) / NS;
+    const unsigned items = runs * groups;
+    const unsigned per_xcd = (items + 7) / 8;
+    const unsigned first = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const unsigned end = min(items, ((blockIdx.x & 7) + 1) * per_xcd);
+    const unsigned stride = gridDim.x >> 3;
     if (first >= end)
         return;
 
     float4 *hl = (float4 *)smem;
-    float *buf = (float *)(smem + kFeSmemProto) + w * kFeBufFloats;
-    uint8_t *codes = smem + kFeSmemProto + kFeWaves * kFeBufFloats * sizeof(float);
+    float2 *wt = (float2 *)(smem + kFeSmemProto);
+    float2 *buf = wt + kFeWtEntries + w * (kFeBufFloats / 2);
+    uint8_t *codes = smem + kFeSmemBase;
 
     // the prototype into LDS: float4 (k, t4, l) at (k * 8 + t4) * 64 + l
     for (int idx = threadIdx.x; idx < kFeTaps * 8 * 64; idx += kFeThreads) {
         const int k = idx >> 9, t4 = (idx >> 6) & 7, l = idx & 63;
         hl[idx] = *(const float4 *)(a.h + k * kFeP + 32 * l + 4 * t4);
     }
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        if (v % kFeWaves == w) {
+            const cf t = unpack_twiddle(cf{kW2048.re[lane], kW2048.im[lane]}, v);
+            const float2 w2 = make_float2(t.r, t.i);
+            wt[2 * lane + (v & 1) + 130 * (v >> 1)] = w2;
+            if (lane == 0 && v > 0)
+                wt[128 + ((v - 1) & 1) + 130 * ((v - 1) >> 1)] = w2;
+            if (lane == 0 && v == 8)
+                wt[129 + 130 * 7] = w2;
+        }
     __syncthreads();
 
-    const FeBases bases{cf{kW1024.re[lane], kW1024.im[lane]}, cf{kW64.re[lane & 3], kW64.im[lane & 3]},
-                        cf{kW2048.re[lane], kW2048.im[lane]}};
+    const FeBases bases{cf{kW1024.re[lane], kW1024.im[lane]}, cf{kW64.re[lane >> 4], kW64.im[lane >> 4]}};
     // this wave's jobs: (item, ii) for items first, first + stride, ... and
-    // ii < 4; the next job's samples are loaded while the current one runs
-    auto input_of = [&](int64_t it, int ii) { return (int)(it / a.n_spectra) * kFeGroup + w * kFeInputsPerWave + ii; };
-    FeRaw raw;
-    fe_load(a, input_of(first, 0), first % a.n_spectra, raw);
-    for (int64_t it = first; it < end; it += stride) {
-        const int64_t m = it % a.n_spectra;
-        const int g = (int)(it / a.n_spectra);
+    // ii < kFeInputsPerWave; the next job's samples are loaded while the
+    // current one is transformed
+    FeRaw<NS> raw;
+    unsigned run = first % runs, g = first / runs;
+    fe_load<NS>(a, g * kFeGroup + w * kFeInputsPerWave, NS * run, raw);
+    for (unsigned it = first; it < end; it += stride) {
+        const int m = NS * run;
+        const unsigned nrun = (it + stride) % runs, ng = (it + stride) / runs;
+#pragma unroll 1
         for (int ii = 0; ii < kFeInputsPerWave; ++ii) {
             const int input = g * kFeGroup + w * kFeInputsPerWave + ii;
-            cf z[16];
-            fe_fir(raw, hl, z);
+            cf z[NS][16];
+            fe_fir<NS>(raw, hl, z);
             if (ii + 1 < kFeInputsPerWave)
-                fe_load(a, input + 1, m, raw);
+                fe_load<NS>(a, input + 1, m, raw);
             else if (it + stride < end)
-                fe_load(a, input_of(it + stride, 0), (it + stride) % a.n_spectra, raw);
-            // this input's EQ gains, loaded before the transform so that
-            // their latency is hidden behind it
-            float gv16[16];
+                fe_load<NS>(a, ng * kFeGroup + w * kFeInputsPerWave, NS * nrun, raw);
             if constexpr (CODES) {
+                // this input's EQ gains, loaded halfway through the transform:
+                // late enough to leave its first half the registers, early
+                // enough to hide their latency
                 const float *gi = a.gains + (int64_t)input * kFeN;
+                float g1[8], g2[8];
+                auto load_gains = [&]() {
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    gv16[v] = gi[lane + 64 * v];
-            }
-            cf y[16];
-            fe_fft(z, bases, buf, y);
-            if constexpr (CODES) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int c = lane + 64 * v;
-                    const float gv = gv16[v];
-                    const int re = quant4(gv * y[v].r), im = quant4(gv * y[v].i);
-                    codes[c * kFeCodeStride + w * kFeInputsPerWave + ii] = (uint8_t)(((re & 15) << 4) | (im & 15));
-                }
+                    for (int v = 0; v < 8; ++v) {
+                        g1[v] = gi[lane + 64 * v];
+                        g2[v] = gi[v == 0 && lane == 0 ? kFeN / 2 : kFeN - lane - 64 * v];
+                    }
+                };
+                uint8_t *const c1 = codes + lane * kFeCodeStride + w * kFeInputsPerWave + ii;
+                uint8_t *const c2 = codes + (kFeN - lane) * kFeCodeStride + w * kFeInputsPerWave + ii;
+                uint8_t *const c0 = lane == 0 ? c2 - kFeN / 2 * kFeCodeStride : c2;
+                fe_fft<NS>(z, bases, buf, wt, load_gains, [&](int s, int v, bool second, cf y) {
+                    // every wave has copied the previous item's codes out
+                    // before the first code of this item is written
+                    if (s == 0 && v == 0 && !second && ii == 0)
+                        lds_barrier();
+                    uint8_t *const c = !second ? c1 : v == 0 ? c0 : c2;
+                    c[(second ? -64 : 64) * v * kFeCodeStride + s * kFeN * kFeCodeStride] =
+                        (uint8_t)pack_code(second ? g2[v] : g1[v], y);
+                });
             } else {
                 float2 *o = (float2 *)a.out + ((int64_t)input * a.n_spectra + m) * kFeN;
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    o[lane + 64 * v] = make_float2(y[v].r, y[v].i);
+                fe_fft<NS>(z, bases, buf, wt, []() {}, [&](int s, int v, bool second, cf y) {
+                    const int c = !second ? lane + 64 * v : v == 0 && lane == 0 ? kFeN / 2 : kFeN - lane - 64 * v;
+                    if (m + s < a.n_spectra)
+                        o[s * kFeN + c] = make_float2(y.r, y.i);
+                });
             }
         }
         if constexpr (CODES) {
-            __syncthreads();
-            // one 16-byte row per channel: out[m][c][16 g ..]
-            uint8_t *o = (uint8_t *)a.out + (m * kFeN) * (int64_t)a.N + g * kFeGroup;
+            lds_barrier();
+            // one 16-byte row per (spectrum, channel): out[m][c][16 g ..]
+            // (an opaque thread index: no address kept across the transforms)
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            uint8_t *o = (uint8_t *)a.out + ((int64_t)m * kFeN) * a.N + g * kFeGroup;
 #pragma unroll
-            for (int c = threadIdx.x; c < kFeN; c += kFeThreads) {
+            for (int k = 0; k < NS * kFeN / kFeThreads; ++k) {
+                const int c = tid + k * kFeThreads;   // (spectrum, channel)
                 const uint32_t *row = (const uint32_t *)(codes + c * kFeCodeStride);
-                *(uint4 *)(o + (int64_t)c * a.N) = make_uint4(row[0], row[1], row[2], row[3]);
+                if (NS == 1 || m + c / kFeN < a.n_spectra)
+                    *(uint4 *)(o + (int64_t)c * a.N) = make_uint4(row[0], row[1], row[2], row[3]);
             }
-            __syncthreads();
         }
+        run = nrun;
+        g = ng;
     }
 }
+#pragma clang fp contract(fast)
 
-constexpr int kFeSmemCodes = kFeSmemProto + kFeWaves * kFeBufFloats * 4 + kFeN * kFeCodeStride;
-constexpr int kFeSmemSpectra = kFeSmemProto + kFeWaves * kFeBufFloats * 4;
-
+template <int NS>
 __global__ __launch_bounds__(kFeThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void xc_fengine_kernel(const FeArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[kFeSmemCodes];
-    fengine_body<true>(smem, a);
+    __shared__ __attribute__((aligned(16))) uint8_t smem[fe_smem_bytes(true, NS)];
+    fengine_body<true, NS>(smem, a);
 }
 
+template <int NS>
 __global__ __launch_bounds__(kFeThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void xc_pfb_spectra_kernel(const FeArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t smem[kFeSmemSpectra];
-    fengine_body<false>(smem, a);
+    __shared__ __attribute__((aligned(16))) uint8_t smem[fe_smem_bytes(false, NS)];
+    fengine_body<false, NS>(smem, a);
 }
 
-// persistent grid: kFeWgsPerCu work-groups per compute unit, a multiple of 8
-// (one run of items per XCD), no more than there are items per XCD
-int fe_grid(int64_t items)
+int fe_cu_count()
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
         cus = 256;
-    const int64_t per_xcd = (items + 7) / 8;
-    return 8 * (int)std::max<int64_t>(1, std::min<int64_t>(cus / 8 * kFeWgsPerCu, per_xcd));
+    return cus;
+}
+
+// Persistent grid: kFeWgsPerCu work-groups per compute unit, a multiple of 8
+// (one run of items per XCD), no more than there are items per XCD.  Two
+// spectra to an item once items of one would give some compute unit more than
+// one: an item of two costs about 1.6 of one.
+template <class K1, class K2>
+hipError_t fe_launch(K1 one, K2 two, const FeArgs &a, hipStream_t s)
+{
+    const int cus = fe_cu_count();
+    const int64_t groups = a.N / kFeGroup, pairs = ((int64_t)a.n_spectra + 1) / 2 * groups;
+    const bool both = a.n_spectra * groups > (int64_t)cus * kFeWgsPerCu;
+    const int64_t per_xcd = ((both ? pairs : a.n_spectra * groups) + 7) / 8;
+    const int grid = 8 * (int)std::max<int64_t>(1, std::min<int64_t>(cus / 8 * kFeWgsPerCu, per_xcd));
+    if (both)
+        hipLaunchKernelGGL(two, dim3(grid), dim3(kFeThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(one, dim3(grid), dim3(kFeThreads), 0, s, a);
+    return hipGetLastError();
 }
 
 int fe_check(const void *adc, int64_t S, int32_t N, const float *h, int64_t n_spectra, const void *out)
@@ -512,10 +683,9 @@ extern "C" int xcorr_fengine(const void *d_adc, int64_t n_samples, int32_t n_inp
     const int64_t items = n_spectra * (n_inputs / kFeGroup);
     if (items > (int64_t)1 << 30)
         return XCORR_E_INVAL;
-    FeArgs a{(const int8_t *)d_adc, n_samples, n_inputs, d_coeffs, d_gains, n_spectra, d_out};
-    const int grid = fe_grid(items);
-    hipLaunchKernelGGL(xc_fengine_kernel, dim3(grid), dim3(kFeThreads), 0, reinterpret_cast<hipStream_t>(stream), a);
-    const hipError_t e = hipGetLastError();
+    FeArgs a{(const int8_t *)d_adc, n_samples, n_inputs, d_coeffs, d_gains, (int)n_spectra, d_out};
+    const hipError_t e =
+        fe_launch(xc_fengine_kernel<1>, xc_fengine_kernel<2>, a, reinterpret_cast<hipStream_t>(stream));
     return e == hipSuccess ? XCORR_OK : api_error(XCORR_E_HIP, std::string("fengine launch: ") + hipGetErrorString(e));
 }
 
@@ -529,10 +699,8 @@ extern "C" int xcorr_pfb_spectra(const void *d_adc, int64_t n_samples, int32_t n
     const int64_t items = n_spectra * (n_inputs / kFeGroup);
     if (items > (int64_t)1 << 30)
         return XCORR_E_INVAL;
-    FeArgs a{(const int8_t *)d_adc, n_samples, n_inputs, d_coeffs, nullptr, n_spectra, d_out};
-    const int grid = fe_grid(items);
-    hipLaunchKernelGGL(xc_pfb_spectra_kernel, dim3(grid), dim3(kFeThreads), 0, reinterpret_cast<hipStream_t>(stream),
-                       a);
-    const hipError_t e = hipGetLastError();
+    FeArgs a{(const int8_t *)d_adc, n_samples, n_inputs, d_coeffs, nullptr, (int)n_spectra, d_out};
+    const hipError_t e =
+        fe_launch(xc_pfb_spectra_kernel<1>, xc_pfb_spectra_kernel<2>, a, reinterpret_cast<hipStream_t>(stream));
     return e == hipSuccess ? XCORR_OK : api_error(XCORR_E_HIP, std::string("pfb launch: ") + hipGetErrorString(e));
 }

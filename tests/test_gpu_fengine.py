@@ -178,3 +178,29 @@ def test_fengine_refusals():
     with pytest.raises(X.XcorrError):
         X.xcorr_fengine(torch.zeros((16, 3 * P), dtype=torch.int8, device=DEV), h, g, out, 1)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("odd", [0, 1], ids=["even", "odd"])
+def test_two_spectra_at_a_time(odd):
+    """Enough spectra that every item holds two (more items of one than
+    compute units), an even and an odd count (the last item then holds one,
+    and its second would need samples past the end): codes against the
+    oracle, and codes and spectra equal to those of short calls, which run
+    one spectrum at a time, byte for byte."""
+    N, M = 16, torch.cuda.get_device_properties(DEV).multi_processor_count + 2 + odd
+    _say(f"two spectra at a time N={N} M={M}")
+    adc, gains = _inputs(N, M, seed=300 + odd)
+    got = _gpu_codes(adc, gains)
+    _check_codes(got, adc, gains)
+    d, g, h = adc.to(DEV), gains.to(DEV), _coeffs()
+    spec = torch.empty((N, M, F, 2), dtype=torch.float32, device=DEV)
+    X.xcorr_pfb_spectra(d, h, spec, M)
+    for m0, n in ((0, 3), (M // 2 | 1, 2), (M - 3, 3)):
+        part = d[:, m0 * P:(m0 + n + TAPS - 1) * P].contiguous()
+        one = torch.empty((n, F, N), dtype=torch.uint8, device=DEV)
+        X.xcorr_fengine(part, h, g, one, n)
+        s1 = torch.empty((N, n, F, 2), dtype=torch.float32, device=DEV)
+        X.xcorr_pfb_spectra(part, h, s1, n)
+        torch.cuda.synchronize()
+        assert np.array_equal(one.cpu().numpy(), got[m0:m0 + n])
+        assert torch.equal(s1, spec[:, m0:m0 + n])
