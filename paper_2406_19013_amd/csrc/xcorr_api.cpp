@@ -246,15 +246,38 @@ void note_ingest(xcorr_ctx *ctx, int64_t n_samples, uint64_t seq)
     ++ctx->ingests;
 }
 
+// The library chooses the kernel of a 4+4-bit launch unless the config names
+// a tile (whose kernels then run) or the environment another family.
+bool free_choice(const xcorr_ctx *ctx) { return ctx->k4 == Kernel4::Gauss && ctx->cfg.tile == 0; }
+
+// Rows of this array that start on 4-byte boundaries, which LDS-DMA needs
+// (and offsets within a 64-sample chunk that fit its 32 bits).
+bool word_rows(const xcorr_config &c, const void *v)
+{
+    return c.n_inputs % 4 == 0 && (uintptr_t)v % 4 == 0 && 64LL * c.n_chans * c.n_inputs < (1LL << 31) - 16;
+}
+
 // One 4+4-bit int8-MFMA launch of the kernel family the context runs:
 // results to `out`, running sums (accumulate = 1) from acc_in (default out).
 hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out, int accumulate, hipStream_t s,
                    const int2 *acc_in = nullptr)
 {
     const xcorr_config &c = ctx->cfg;
-    if (gauss_runs(ctx->k4, ctx->plan, c.n_chans, c.n_inputs) && (uintptr_t)v % 16 == 0)
-        return xc::launch_gauss4(ctx->plan, v, T, c.n_chans, c.n_inputs, out, accumulate, s, acc_in);
-    return xc::launch_mfma4f(ctx->plan, v, T, c.n_chans, c.n_inputs, out, accumulate, s, acc_in);
+    const int F = c.n_chans, N = c.n_inputs;
+    if (free_choice(ctx)) {
+        if (word_rows(c, v)) {
+            if (xc::gauss4_runs(ctx->plan, F, N)) {
+                const int rb = xc::split4_blocks(ctx->plan, F, N, T);
+                return rb ? xc::launch_split4(rb, v, T, F, N, out, accumulate, s, acc_in)
+                          : xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
+            }
+        } else if (xc::split4_unaligned(F, N, T)) {
+            return xc::launch_split4(1, v, T, F, N, out, accumulate, s, acc_in);
+        }
+    }
+    if (gauss_runs(ctx->k4, ctx->plan, F, N) && (uintptr_t)v % 16 == 0)
+        return xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
+    return xc::launch_mfma4f(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
 }
 
 // The current device must be a gfx950 GPU.
@@ -500,7 +523,12 @@ int xcorr_ingest_blocks(xcorr_ctx *ctx, const void *const *d_blocks, int n_block
             bt.p[b] = static_cast<const uint8_t *>(d_blocks[b0 + b]);
         bt.chunks_per_block = (int)(block_samples / 64);
         const int accumulate = (ctx->acc_samples > 0 || b0 > 0) ? 1 : 0;
-        const hipError_t e = gauss_runs(ctx->k4, ctx->plan, c.n_chans, c.n_inputs)
+        const bool gauss = gauss_runs(ctx->k4, ctx->plan, c.n_chans, c.n_inputs);
+        const int rb = gauss && free_choice(ctx)
+                           ? xc::split4_blocks(ctx->plan, c.n_chans, c.n_inputs, n * block_samples) : 0;
+        const hipError_t e = rb ? xc::launch_split4_blocks(rb, bt, n, c.n_chans, c.n_inputs,
+                                                           static_cast<int2 *>(ctx->ws), accumulate, s)
+                             : gauss
                                  ? xc::launch_gauss4_blocks(ctx->plan, bt, n, c.n_chans, c.n_inputs,
                                                             static_cast<int2 *>(ctx->ws), accumulate, s)
                                  : xc::launch_mfma4f_blocks(ctx->plan, bt, n, c.n_chans, c.n_inputs,

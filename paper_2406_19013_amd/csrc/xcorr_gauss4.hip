@@ -138,18 +138,20 @@ hipError_t launch_any(int D, int nseg, const uint8_t *volts, int64_t T, int F, i
 
 }  // namespace
 
-bool gauss4_supported(const Plan &pl, int F, int N)
+bool gauss4_runs(const Plan &pl, int F, int N)
 {
     const bool shape = pl.nseg == 1 ? (pl.D >= 1 && pl.D <= 6 && N <= 32 * pl.D)
                                     : (pl.D >= 1 && pl.D <= 4 && pl.nseg * pl.D * 32 >= N);
-    return shape && N % 16 == 0 && F >= 1 && 64LL * F * N < (1LL << 31) - 16 &&
+    return shape && N % 4 == 0 && F >= 1 && 64LL * F * N < (1LL << 31) - 16 &&
            (int64_t)F * pl.regions < (1LL << 30);
 }
+
+bool gauss4_supported(const Plan &pl, int F, int N) { return N % 16 == 0 && gauss4_runs(pl, F, N); }
 
 hipError_t launch_gauss4(const Plan &pl, const uint8_t *volts, int64_t T, int F, int N, int2 *acc, int accumulate,
                          hipStream_t s, const int2 *acc_in)
 {
-    if (!gauss4_supported(pl, F, N) || T < 1 || T > kMaxSamplesPerLaunch4 || !volts || (uintptr_t)volts % 16 ||
+    if (!gauss4_runs(pl, F, N) || T < 1 || T > kMaxSamplesPerLaunch4 || !volts || (uintptr_t)volts % 4 ||
         !acc)
         return hipErrorInvalidValue;
     return launch_any(pl.D, pl.nseg, volts, T, F, N, acc, acc_in ? acc_in : acc, nullptr, accumulate, s);

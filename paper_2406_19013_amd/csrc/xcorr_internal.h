@@ -90,13 +90,31 @@ hipError_t launch_mfma4f_blocks(const Plan &pl, const BlockTable &bt, int n_bloc
 
 // Three-product kernel (4+4-bit, int8 MFMA): persistent; a whole triangle per
 // channel (N <= 32 D, D <= 6) or segments of D <= 4 blocks with the rectangles
-// between them (two launches); N a multiple of 16, 16-byte-aligned input.
+// between them (two launches).  It takes rows on 4-byte boundaries (N a
+// multiple of 4, 4-byte-aligned input: gauss4_runs); tile plans, the tuner and
+// the batch count it as theirs for N a multiple of 16 (gauss4_supported).
 // acc_in as for launch_mfma4f.
+bool gauss4_runs(const Plan &pl, int F, int N);
 bool gauss4_supported(const Plan &pl, int F, int N);
 hipError_t launch_gauss4(const Plan &pl, const uint8_t *volts, int64_t T, int F, int N, int2 *acc, int accumulate,
                          hipStream_t s, const int2 *acc_in = nullptr);
 hipError_t launch_gauss4_blocks(const Plan &pl, const BlockTable &bt, int n_blocks, int F, int N, int2 *acc,
                                 int accumulate, hipStream_t s, const int2 *acc_in = nullptr);
+
+// Time-split kernel (4+4-bit, int8 MFMA): a work-group per (channel, region of
+// rb x rb blocks), rb = 1 or 2, whose waves share the region's samples; any N
+// and alignment (rb = 2 falls back to 1 where rows are not 4-byte aligned).
+// The block-table form needs N a multiple of 16 and 16-byte-aligned blocks.
+hipError_t launch_split4(int rb, const uint8_t *volts, int64_t T, int F, int N, int2 *acc, int accumulate,
+                         hipStream_t s, const int2 *acc_in = nullptr);
+// Which launches it takes: split4_blocks returns the region size for an
+// array with 4-byte-aligned rows, 0 where the persistent kernel with plan pl is
+// the faster; split4_unaligned is for other rows, where the alternative is
+// launch_mfma4f.
+int split4_blocks(const Plan &pl, int F, int N, int64_t T);
+bool split4_unaligned(int F, int N, int64_t T);
+hipError_t launch_split4_blocks(int rb, const BlockTable &bt, int n_blocks, int F, int N, int2 *acc, int accumulate,
+                                hipStream_t s);
 
 // Batched launch (4+4-bit, int8 MFMA) over up to kMaxBatchArrays arrays of
 // uneven N, F and sample counts; the descriptors travel by value in the kernel
