@@ -52,3 +52,14 @@ def test_refusals():
     v = torch.zeros((1, 6, 2), dtype=torch.int32, device=DEV)
     with pytest.raises(X.XcorrError):
         X.xcorr_stokes(v, 3)
+
+
+@pytest.mark.parametrize("N,F", [(18, 5), (22, 8), (514, 2), (1030, 1)])
+def test_channel_groups_and_many_feeds(N, F):
+    """Channel counts on both sides of the four a thread takes, pair counts
+    off the work-group's 64, and many feeds (the pair index is found from a
+    float square root)."""
+    rng = np.random.default_rng(N + F)
+    v = rng.integers(-2 ** 31, 2 ** 31, size=(F, N * (N + 1) // 2, 2), dtype=np.int64).astype(np.int32)
+    got = X.xcorr_stokes(torch.from_numpy(v).to(DEV), N).cpu().numpy()
+    assert np.array_equal(got, st.stokes(v, N))
