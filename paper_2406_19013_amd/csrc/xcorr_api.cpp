@@ -280,6 +280,21 @@ hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out,
     return xc::launch_mfma4f(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
 }
 
+// One MFMA-path launch of either sample format (not the per-role kernel):
+// results to `out`, running sums (accumulate = 1) from acc_in.
+hipError_t launch_mfma(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, void *out, int accumulate, hipStream_t s,
+                       const void *acc_in)
+{
+    const xcorr_config &c = ctx->cfg;
+    if (c.sample_bits == 4)
+        return launch4(ctx, v, T, static_cast<int2 *>(out), accumulate, s, static_cast<const int2 *>(acc_in));
+    // as for 4+4-bit launches, the library chooses unless the config names a tile
+    const bool f16 = c.path == XCORR_PATH_F16_MFMA;
+    const int rb = c.tile ? 0 : xc::split8_blocks(ctx->plan, f16, v, c.n_chans, c.n_inputs, T);
+    return rb ? xc::launch_split8(rb, f16, v, T, c.n_chans, c.n_inputs, out, acc_in, accumulate, s)
+              : xc::launch_mfma8(ctx->plan, f16, v, T, c.n_chans, c.n_inputs, out, acc_in, accumulate, s);
+}
+
 // The current device must be a gfx950 GPU.
 int device_check()
 {
@@ -428,11 +443,8 @@ int xcorr_ingest(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, uint64_
             e = xc::launch_plain(c.sample_bits, vp, tl, c.n_chans, c.n_inputs, acc, accumulate, s);
         else if (c.sample_bits == 4 && ctx->k4 == Kernel4::Roles)
             e = xc::launch_mfma4(ctx->plan, ctx->kc, vp, tl, c.n_chans, c.n_inputs, acc, accumulate, s);
-        else if (c.sample_bits == 4)
-            e = launch4(ctx, vp, tl, acc, accumulate, s);
         else
-            e = xc::launch_mfma8(ctx->plan, c.path == XCORR_PATH_F16_MFMA, vp, tl, c.n_chans, c.n_inputs,
-                                 ctx->ws, accumulate, s);
+            e = launch_mfma(ctx, vp, tl, acc, accumulate, s, acc);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
         ++ctx->launches;
@@ -453,24 +465,22 @@ int xcorr_ingest_dump(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, ui
     if ((uintptr_t)d_out % 16)
         return set_error(XCORR_E_INVAL, "d_out must be 16-byte aligned");
     const xcorr_config &c = ctx->cfg;
-    if (!(c.sample_bits == 4 && c.path == XCORR_PATH_I8_MFMA && ctx->k4 != Kernel4::Roles)) {
+    if (c.path == XCORR_PATH_PLAIN || (c.sample_bits == 4 && ctx->k4 == Kernel4::Roles)) {
         const int rc = xcorr_ingest(ctx, d_volts, n_samples, seq, stream);
         return rc ? rc : xcorr_dump(ctx, d_out, n_integrated, n_gaps, stream);
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const uint8_t *v = static_cast<const uint8_t *>(d_volts);
-    int2 *acc = static_cast<int2 *>(ctx->ws);
-    const int64_t bytes_per_row = (int64_t)c.n_chans * c.n_inputs;
-    const int64_t L = xc::kMaxSamplesPerLaunch4;
+    const int64_t bytes_per_row = (int64_t)c.n_chans * c.n_inputs * (c.sample_bits == 4 ? 1 : 2);
+    const int64_t L = c.sample_bits == 4 ? xc::kMaxSamplesPerLaunch4 : xc::kMaxSamplesPerLaunch8;
     for (int64_t t0 = 0; t0 < n_samples; t0 += L) {
         const int64_t tl = std::min<int64_t>(L, n_samples - t0);
         const int accumulate = (ctx->acc_samples > 0 || t0 > 0) ? 1 : 0;
         const bool last = t0 + tl >= n_samples;
         // the last launch adds the running sums to its own and writes the
         // result to d_out: the integration ends without a copy
-        const hipError_t e = last ? launch4(ctx, v + t0 * bytes_per_row, tl, static_cast<int2 *>(d_out),
-                                            accumulate, s, acc)
-                                  : launch4(ctx, v + t0 * bytes_per_row, tl, acc, accumulate, s);
+        const hipError_t e = launch_mfma(ctx, v + t0 * bytes_per_row, tl, last ? d_out : ctx->ws, accumulate, s,
+                                         ctx->ws);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
         ++ctx->launches;
@@ -922,7 +932,7 @@ static int autotune_impl(const xcorr_config *cfg, void *d_scratch, size_t scratc
                 return xc::launch_batch4(args, queue, vec, (int)std::min<int64_t>(cus, items), s);
             }
             if (c.sample_bits == 8)
-                return xc::launch_mfma8(pl, c.path == XCORR_PATH_F16_MFMA, volts, T, c.n_chans, c.n_inputs, acc,
+                return xc::launch_mfma8(pl, c.path == XCORR_PATH_F16_MFMA, volts, T, c.n_chans, c.n_inputs, acc, acc,
                                         accumulate, s);
             if (k4 == Kernel4::Roles)
                 return xc::launch_mfma4(pl, 64, volts, T, c.n_chans, c.n_inputs, static_cast<int2 *>(acc),

@@ -58,22 +58,24 @@ hipError_t launch_mfma4(const Plan &pl, int kc, const uint8_t *volts, int64_t T,
 hipError_t launch_mfma4f(const Plan &pl, const uint8_t *volts, int64_t T, int F, int N, int2 *acc,
                          int accumulate, hipStream_t s, const int2 *acc_in = nullptr);
 // 8+8-bit input, int8 MFMA (f16 = false, int2 accumulators) or FP16 MFMA with
-// FP32 accumulation (f16 = true, float2 accumulators).
+// FP32 accumulation (f16 = true, float2 accumulators); accumulate = 1 adds the
+// running sums at acc_in (acc itself, or the accumulators when the result goes
+// to a caller's dump buffer).
 hipError_t launch_mfma8(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N, void *acc,
-                        int accumulate, hipStream_t s);
+                        const void *acc_in, int accumulate, hipStream_t s);
 // per-D launchers of the 8+8-bit kernels (xcorr_mfma8.hip compiled with -DXC_D=d)
 hipError_t launch_mfma8_d1(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_mfma8_d2(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_mfma8_d3(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_mfma8_d4(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_mfma8_d5(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_mfma8_d6(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                          void *acc, int accumulate, hipStream_t s);
+                          void *acc, const void *acc_in, int accumulate, hipStream_t s);
 
 hipError_t launch_dump(const void *acc, void *out, int64_t bytes, int empty, hipStream_t s);
 
@@ -110,9 +112,15 @@ hipError_t launch_split4(int rb, const uint8_t *volts, int64_t T, int F, int N, 
 // Which launches it takes: split4_blocks returns the region size for an
 // array with 4-byte-aligned rows, 0 where the persistent kernel with plan pl is
 // the faster; split4_unaligned is for other rows, where the alternative is
-// launch_mfma4f.
+// launch_mfma4f.  split8_blocks: the region size for any 8+8-bit input, 0 where
+// launch_mfma8 with plan pl is the faster.
 int split4_blocks(const Plan &pl, int F, int N, int64_t T);
 bool split4_unaligned(int F, int N, int64_t T);
+int split8_blocks(const Plan &pl, bool f16, const uint8_t *volts, int F, int N, int64_t T);
+// 8+8-bit form (int8, or FP16 with float2 sums); rows are 4-byte aligned when N
+// is even.
+hipError_t launch_split8(int rb, bool f16, const uint8_t *volts, int64_t T, int F, int N, void *acc,
+                         const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_split4_blocks(int rb, const BlockTable &bt, int n_blocks, int F, int N, int2 *acc, int accumulate,
                                 hipStream_t s);
 

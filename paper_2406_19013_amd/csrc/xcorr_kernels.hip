@@ -176,17 +176,17 @@ hipError_t launch_plain(int bits, const uint8_t *volts, int64_t T, int F, int N,
 }
 
 hipError_t launch_mfma8(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N, void *acc,
-                        int accumulate, hipStream_t s)
+                        const void *acc_in, int accumulate, hipStream_t s)
 {
     if (!plan_supported(N, pl.D))
         return hipErrorInvalidValue;
     switch (pl.D) {
-    case 1: return launch_mfma8_d1(pl, f16, volts, T, F, N, acc, accumulate, s);
-    case 2: return launch_mfma8_d2(pl, f16, volts, T, F, N, acc, accumulate, s);
-    case 3: return launch_mfma8_d3(pl, f16, volts, T, F, N, acc, accumulate, s);
-    case 4: return launch_mfma8_d4(pl, f16, volts, T, F, N, acc, accumulate, s);
-    case 5: return launch_mfma8_d5(pl, f16, volts, T, F, N, acc, accumulate, s);
-    case 6: return launch_mfma8_d6(pl, f16, volts, T, F, N, acc, accumulate, s);
+    case 1: return launch_mfma8_d1(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
+    case 2: return launch_mfma8_d2(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
+    case 3: return launch_mfma8_d3(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
+    case 4: return launch_mfma8_d4(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
+    case 5: return launch_mfma8_d5(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
+    case 6: return launch_mfma8_d6(pl, f16, volts, T, F, N, acc, acc_in, accumulate, s);
     default: return hipErrorInvalidValue;
     }
 }

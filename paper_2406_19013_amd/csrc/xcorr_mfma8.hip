@@ -161,7 +161,7 @@ constexpr int mfma8_smem_bytes(int KC, int D)
 template <int D, bool TRI, bool F16, int KC, int NBUF, int VEC, int PROD, int PAR, int HALF>
 __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__restrict__ volts, int64_t T,
                                              int F, int N, int f, int row_blk, int col_blk,
-                                             void *__restrict__ acc_out, int accumulate)
+                                             void *acc_out, const void *acc_in, int accumulate)
 {
     using AccT = typename std::conditional<F16, v16f, v16i>::type;
     constexpr int T0 = half_begin(D, TRI, HALF), T1 = half_end(D, TRI, HALF);
@@ -348,7 +348,7 @@ __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__res
                     float2 *const dst = static_cast<float2 *>(acc_out) + (int64_t)f * P;
                     float2 o[4];
                     if (accumulate)
-                        quad_running_sums(dst, p, i0, j, diag, N, o);
+                        quad_running_sums(static_cast<const float2 *>(acc_in) + (int64_t)f * P, p, i0, j, diag, N, o);
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
                         const int i = i0 + m;
@@ -370,7 +370,7 @@ __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__res
                     int2 *const dst = static_cast<int2 *>(acc_out) + (int64_t)f * P;
                     int2 o[4];
                     if (accumulate)
-                        quad_running_sums(dst, p, i0, j, diag, N, o);
+                        quad_running_sums(static_cast<const int2 *>(acc_in) + (int64_t)f * P, p, i0, j, diag, N, o);
 #pragma unroll
                     for (int m = 0; m < 4; ++m) {
                         const int i = i0 + m;
@@ -399,13 +399,13 @@ __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__res
 template <int D, bool TRI, bool F16, int KC, int NBUF, int VEC>
 __device__ __forceinline__ void mfma8_dispatch(uint8_t *smem, const uint8_t *__restrict__ volts, int64_t T,
                                                int F, int N, int f, int row_blk, int col_blk,
-                                               void *__restrict__ acc_out, int accumulate)
+                                               void *acc_out, const void *acc_in, int accumulate)
 {
     switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
 #define XC_CASE8(W)                                                                                     \
     case W:                                                                                             \
         mfma8_region<D, TRI, F16, KC, NBUF, VEC, ((W) & 1), (((W) >> 1) & 1), ((W) >> 2)>(            \
-            smem, volts, T, F, N, f, row_blk, col_blk, acc_out, accumulate);                            \
+            smem, volts, T, F, N, f, row_blk, col_blk, acc_out, acc_in, accumulate);                    \
         break;
         XC_CASE8(0) XC_CASE8(1) XC_CASE8(2) XC_CASE8(3) XC_CASE8(4) XC_CASE8(5) XC_CASE8(6) XC_CASE8(7)
 #undef XC_CASE8
@@ -416,7 +416,7 @@ __device__ __forceinline__ void mfma8_dispatch(uint8_t *smem, const uint8_t *__r
 template <int D, bool F16, int KC, int VEC>
 __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void xc_mfma8_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N, int nseg, int R,
-                     int nitems, void *__restrict__ acc_out, int accumulate)
+                     int nitems, void *acc_out, const void *acc_in, int accumulate)
 {
     constexpr int NBUF = mfma8_nbuf();
     __shared__ __attribute__((aligned(1024))) uint8_t smem[mfma8_smem_bytes(KC, D)];
@@ -428,7 +428,7 @@ void xc_mfma8_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N,
     const int f = item / R;
     const int r = item - f * R;
     if (r < nseg) {
-        mfma8_dispatch<D, true, F16, KC, NBUF, VEC>(smem, volts, T, F, N, f, r * D, r * D, acc_out, accumulate);
+        mfma8_dispatch<D, true, F16, KC, NBUF, VEC>(smem, volts, T, F, N, f, r * D, r * D, acc_out, acc_in, accumulate);
     } else if constexpr (D <= 4) {
         const int k = r - nseg;
         int a = (int)((1.f + sqrtf(1.f + 8.f * k)) * 0.5f);
@@ -437,7 +437,7 @@ void xc_mfma8_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N,
         while ((a + 1) * a / 2 <= k)
             ++a;
         const int b = k - a * (a - 1) / 2;
-        mfma8_dispatch<D, false, F16, KC, NBUF, VEC>(smem, volts, T, F, N, f, a * D, b * D, acc_out, accumulate);
+        mfma8_dispatch<D, false, F16, KC, NBUF, VEC>(smem, volts, T, F, N, f, a * D, b * D, acc_out, acc_in, accumulate);
     }
 }
 
@@ -445,18 +445,20 @@ void xc_mfma8_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N,
 
 template <int D, bool F16>
 static hipError_t launch_mfma8_t(const Plan &pl, const uint8_t *volts, int64_t T, int F, int N, void *acc,
-                                 int accumulate, hipStream_t s)
+                                 const void *acc_in, int accumulate, hipStream_t s)
 {
     constexpr int KC = 64;
     const int64_t nitems64 = (int64_t)F * pl.regions;
     if (nitems64 > (1LL << 30))
         return hipErrorInvalidValue;
     const int nitems = (int)nitems64;
-    const int vec_ok = (N % 8 == 0) && ((uintptr_t)volts % 16 == 0) &&
+    // LDS-DMA needs rows on 4-byte boundaries; a unit that reaches past input
+    // N - 1 brings other channels' inputs into rows and columns not stored
+    const int vec_ok = (N % 2 == 0) && ((uintptr_t)volts % 4 == 0) &&
                        (int64_t)KC * F * N * 2 < (1LL << 31) - 16;
     auto kern = vec_ok ? xc_mfma8_kernel<D, F16, KC, 1> : xc_mfma8_kernel<D, F16, KC, 0>;
     hipLaunchKernelGGL(kern, dim3(xcd_grid(nitems)), dim3(kMfmaThreads), 0, s, volts, T, F, N, pl.nseg,
-                       pl.regions, nitems, acc, accumulate);
+                       pl.regions, nitems, acc, acc_in, accumulate);
     return hipGetLastError();
 }
 
@@ -464,10 +466,10 @@ static hipError_t launch_mfma8_t(const Plan &pl, const uint8_t *volts, int64_t T
 #define XC_CAT(a, b) XC_CAT2(a, b)
 
 hipError_t XC_CAT(launch_mfma8_d, XC_D)(const Plan &pl, bool f16, const uint8_t *volts, int64_t T, int F, int N,
-                                        void *acc, int accumulate, hipStream_t s)
+                                        void *acc, const void *acc_in, int accumulate, hipStream_t s)
 {
-    return f16 ? launch_mfma8_t<XC_D, true>(pl, volts, T, F, N, acc, accumulate, s)
-               : launch_mfma8_t<XC_D, false>(pl, volts, T, F, N, acc, accumulate, s);
+    return f16 ? launch_mfma8_t<XC_D, true>(pl, volts, T, F, N, acc, acc_in, accumulate, s)
+               : launch_mfma8_t<XC_D, false>(pl, volts, T, F, N, acc, acc_in, accumulate, s);
 }
 
 }  // namespace xc

@@ -115,3 +115,67 @@ def test_unaligned_rows_of_many_channels(N, F, T):
     _say(f"unaligned rows N={N} F={F} T={T}")
     v = _at(synth.uniform_volts4(N, F, T, seed=(2105, N)), 0)
     assert torch.equal(_run(v, N, F, [T]), _run(v, N, F, [T], X.PATH_PLAIN))
+
+
+def _run8(v, N, F, splits, path, last_dumps=False):
+    c = X.Correlator(N, F, 8, path)
+    t0 = 0
+    for k, n in enumerate(splits):
+        if last_dumps and k + 1 == len(splits):
+            out, total, _ = c.ingest_dump(v[t0:t0 + n])
+        else:
+            c.ingest(v[t0:t0 + n], n)
+        t0 += n
+    if not last_dumps:
+        out, total, _ = c.dump()
+    torch.cuda.synchronize()
+    assert total == sum(splits)
+    c.close()
+    return out
+
+
+@pytest.mark.parametrize("T", [1, 15, 17, 128, 145, 300])
+@pytest.mark.parametrize("N,F", [(n, f) for n in (1, 2, 31, 32, 33, 64, 66, 99, 130, 192) for f in (1, 3)])
+def test_8bit_few_channels(N, F, T):
+    """int8 exact; FP16 equal to the float64 oracle (every sum stays an
+    integer below 2^24).  Around the 32-input block, the 64-input region, the
+    16-sample step and the waves' first round of 128."""
+    _say(f"split 8bit N={N} F={F} T={T}")
+    v = synth.uniform_volts8(N, F, T, seed=(2106, N, F, T))
+    d = v.cuda()
+    want = oracle.xcorr(v.numpy(), 8, T, F, N)
+    assert np.array_equal(_run8(d, N, F, [T], X.PATH_I8_MFMA).cpu().numpy(), oracle.to_int32(want))
+    assert np.abs(want).max() < 2 ** 24
+    assert np.array_equal(_run8(d, N, F, [T], X.PATH_F16_MFMA).cpu().numpy().astype(np.float64), want)
+
+
+@pytest.mark.parametrize("path", [X.PATH_I8_MFMA, X.PATH_F16_MFMA], ids=["int8", "fp16"])
+@pytest.mark.parametrize("N,F,offset", [(33, 3, 0), (33, 3, 1), (34, 3, 2), (34, 3, 4), (192, 3, 8), (130, 515, 4),
+                                        (36, 1030, 8), (192, 300, 0)])
+def test_8bit_starts_and_running_sums(N, F, offset, path):
+    """Start addresses off the 16-byte boundaries, few and many channels; the
+    last ingest adds to the running sums straight into the dump."""
+    splits = [70, 33, 90]
+    _say(f"split 8bit N={N} F={F} offset={offset}")
+    v = synth.uniform_volts8(N, F, sum(splits), seed=(2107, N, offset))
+    d = _at(v.view(torch.uint8), offset).view(torch.int8)
+    want = _run8(d, N, F, splits, X.PATH_PLAIN)
+    assert int(want.abs().max()) < 2 ** 24
+    for last_dumps in (False, True):
+        assert torch.equal(_run8(d, N, F, splits, path, last_dumps).to(torch.int32), want)
+
+
+def test_8bit_dumping_ingest_leaves_nothing_behind():
+    """Integrations that end with ingest_dump, one launch and several, one
+    after another on a context."""
+    N, F = 64, 40
+    v = synth.uniform_volts8(N, F, 500, seed=(2108,)).cuda()
+    c = X.Correlator(N, F, 8)
+    spans = [(0, 100, 200), (50, 90), (10, 200, 260, 400)]
+    for span in spans:
+        for a, b in zip(span[:-2], span[1:-1]):
+            c.ingest(v[a:b])
+        out, n, _ = c.ingest_dump(v[span[-2]:span[-1]])
+        assert n == span[-1] - span[0]
+        assert torch.equal(out, _run8(v[span[0]:span[-1]], N, F, [n], X.PATH_PLAIN))
+    c.close()
