@@ -255,7 +255,7 @@ constexpr int g3_mfmas_of(int s)
 // rows of a tile's running sums that an accumulating epilogue requests ahead
 // of its stores: the whole tile where the registers allow, else half of it
 template <int SH>
-constexpr int g3_old_rows(int D) { return (SH == kTri && D <= 3) || (SH == kPair && D >= 4) ? 8 : 16; }
+constexpr int g3_old_rows(int D) { return (SH == kTri && (D <= 3 || D == 6)) || (SH == kPair && D >= 4) ? 8 : 16; }
 
 // LDS transpose slot of a diagonal tile: its block
 template <int D, int SH>
@@ -288,6 +288,24 @@ template <int SH>
 constexpr int g3_gh_bytes(int D) { return g3_blocks<SH>(D) * 32 * 8; }
 template <int SH>
 constexpr int g3_smem_bytes(int D) { return g3_ring_bytes<SH>(D) + g3_tr_bytes<SH>(D) + g3_gh_bytes<SH>(D); }
+
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+
+// Wait until the chunk before the last r chunks a wave issued has arrived,
+// when `after` other memory operations were issued since that chunk as well
+// (operations complete in order; the counter holds at most 63).
+template <int LOADS, int MAXR, int AFTER>
+__device__ __forceinline__ void wait_vmcnt_chunks_after(int r)
+{
+    if constexpr (MAXR > 0) {
+        if (r >= MAXR)
+            wait_vmcnt<(LOADS * MAXR + AFTER < 63 ? LOADS * MAXR + AFTER : 63)>();
+        else
+            wait_vmcnt_chunks_after<LOADS, MAXR - 1, AFTER>(r);
+    } else {
+        wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
+    }
+}
 
 // LDS-only wait: outstanding LDS operations of this wave done, memory
 // operations in flight left alone (vmcnt and expcnt at their maxima).
@@ -476,7 +494,12 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
         });
     };
     // epilogue of one item (channel, region): combine, descale and store this
-    // wave's tiles
+    // wave's tiles.  All waves of the work-group are in it together, so its
+    // length is time the matrix cores are idle (about 8 us per item with a
+    // branch, a 64-bit address and a test per element): rows are clipped by
+    // the buffer's end instead, and the next item's chunks are waited for
+    // without waiting for these stores.  512 inputs x 512 channels x 2048
+    // samples: 578 -> 572 us; a batch of four arrays: 655 -> 636 us.
     auto epilogue = [&](int it) {
         const int fq = it / a.nreg;
         const int f = SH == kPair ? 2 * fq : fq;   // first channel of the item
@@ -520,26 +543,42 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
             constexpr int Ib = second ? I - D : I, Jb = second ? J - D : J;
             const int fch = second ? f + 1 : f;
             if (fch < a.F) {
-            int2 *const out_f = a.out + (int64_t)fch * P;
-            const int2 *const in_f = a.in + (int64_t)fch * P;
+            // Results and running sums go through buffer descriptors that end
+            // with the channel's triangle: a row past input N - 1 lies past
+            // that end, where stores are dropped and loads give 0, so rows
+            // need no test and no branch.
+            const int bytes = (int)(8 * P);
+            const int64_t chan = __builtin_amdgcn_readfirstlane(fch) * P;
+            __amdgpu_buffer_rsrc_t out_f =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(a.out + chan), (short)0, bytes, 0x00020000);
+            __amdgpu_buffer_rsrc_t in_f =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(a.in + chan), (short)0, bytes, 0x00020000);
             // column input: local index for the sums, global for the output
             const int jloc = J * 32 + jl;
             const int j = (SH == kRect ? cb + (J - D) : rb + Jb) * 32 + jl;
+            const int i0 = (rb + Ib) * 32 + il0;   // this lane's first row
             const int2 ghj = *(const int2 *)&gh[jloc * 2];
+            const uint32_t ngj = 0u - (uint32_t)ghj.x, hjT = (uint32_t)ghj.y + 128u * (uint32_t)Tp;
+            // byte offset of entry (i, j): 8 (i (i + 1) / 2 + j), for result
+            // register r: row i0 + 8 (r / 4) + r % 4; past the end above the
+            // diagonal of a diagonal tile
+            auto offset = [&](int r) {
+                const int i = i0 + 8 * (r >> 2);                    // first row of the quad
+                const int u = r & 3;
+                const int off = 4 * (int)__umul24(i, i + 1) + 8 * j + u * (8 * i) + 4 * u * (u + 1);
+                return diag && j > i + u ? kBufferOutOfRange : off;
+            };
             // running sums of the tile's rows (ACC = 1), OR of them at a time
             // (the first group before the transpose), each group requested
             // before the stores it feeds: the elements a thread loads and
             // stores are its own, so the loads need not wait for earlier
-            // stores (a valid address where the pair does not exist)
+            // stores
             constexpr int OR = g3_old_rows<SH>(D);
-            int2 old[ACC ? OR : 1];
+            v2i old[ACC ? OR : 1];
             auto load_old = [&](int r0) {
 #pragma unroll
-                for (int r = 0; r < OR; ++r) {
-                    const int i = (rb + Ib) * 32 + 8 * ((r0 + r) >> 2) + il0 + ((r0 + r) & 3);
-                    const bool ok = i < a.N && (!diag || j <= i);
-                    old[r] = in_f[ok ? (int64_t)i * (i + 1) / 2 + j : 0];
-                }
+                for (int r = 0; r < OR; ++r)
+                    old[r] = __builtin_bit_cast(v2i, __builtin_amdgcn_raw_buffer_load_b64(in_f, offset(r0 + r), 0, 0));
             };
             if constexpr (ACC)
                 load_old(0);
@@ -559,7 +598,6 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 const int ibl = I * 32 + 8 * r4 + il0;                // rows ibl .. ibl + 3 (local)
-                const int ib = (rb + Ib) * 32 + 8 * r4 + il0;         // and their global inputs
                 if constexpr (ACC && OR < 16)
                     if (r4 > 0 && 4 * r4 % OR == 0)
                         load_old(4 * r4);
@@ -570,21 +608,21 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int r = 4 * r4 + u;
-                    const int i = ib + u;
                     const uint32_t ab = (uint32_t)acc_ab[q][r], bav = (uint32_t)ba[r];
                     const uint32_t rr = (uint32_t)acc_rr[q][r];
-                    const int im = (int)(ab - bav + (uint32_t)gi[u] - (uint32_t)ghj.x) >> 5;
-                    const int ii = (int)(2u * rr - ab - bav + (uint32_t)hi[u] + (uint32_t)ghj.y + 128u * (uint32_t)Tp) >> 1;
-                    int re = (acc_rr[q][r] >> 8) + ii;
-                    int imv = im;
+                    // 2 Re = 2 P_rr / 256 + 2 Sum im im, P_rr a multiple of 256
+                    int imv = (int)(ab + (uint32_t)gi[u] + ngj - bav) >> 5;
+                    int re = (int)(2u * rr + (uint32_t)(acc_rr[q][r] >> 7) + (uint32_t)hi[u] + hjT - ab - bav) >> 1;
                     if constexpr (ACC) {
                         re += old[r % OR].x;
                         imv += old[r % OR].y;
                     }
-                    if (i < a.N && (!diag || j <= i))
-                        out_f[(int64_t)i * (i + 1) / 2 + j] = make_int2(re, imv);
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v2i{re, imv}), out_f, offset(r), 0, 0);
                 }
             }
+            // one tile's running sums at a time (registers)
+            if constexpr (ACC)
+                __builtin_amdgcn_sched_barrier(0);
             }
             }
         });
@@ -651,6 +689,11 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
         });
     };
 
+    // Stores of the last epilogue and the number of chunks issued before it:
+    // the wait for one of those chunks leaves the stores in flight.  (An item
+    // without its second channel stores less: counted as none.)
+    constexpr int STORES = 16 * g3_ntiles_of<D, SH>(SLOT);
+    int stored_after = 0;
     int bufc = 0;          // ring slot of chunk gi
     int ck = 0, cc = 0;    // item, and chunk within the item, being computed
     for (int gi = 0; gi < total; ++gi) {
@@ -664,13 +707,16 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
         const bool item_end = cc + 1 == nch;
         if (more && (gi + 1) % CPB == 0) {
             // Next group gi + 1 .. gi + CPB: complete when this wave has at
-            // most the chunks issued after it outstanding (loads complete in
-            // order; the stores of an earlier epilogue only make the wait
-            // longer).  After the barrier every wave has read both steps of
+            // most the chunks (and the epilogue's stores) issued after it
+            // outstanding: memory operations complete in order.  After the
+            // barrier every wave has read both steps of
             // this group's chunks (each waits for its LDS reads first), so
             // their slots take the next chunks of the stream.
             const int last = min(gi + CPB, total - 1);
-            wait_vmcnt_chunks<LOADS, NBUF - 1>(n_issued - 1 - last);
+            if (last < stored_after)
+                wait_vmcnt_chunks_after<LOADS, NBUF - 1, STORES>(n_issued - 1 - last);
+            else
+                wait_vmcnt_chunks<LOADS, NBUF - 1>(n_issued - 1 - last);
             wait_lgkm0();
             barrier_no_fence();
             int slot = bufc - (CPB - 1);
@@ -691,7 +737,9 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
             read_step(nb, 0, X0);
         step(X1);
         if (item_end) {
-            epilogue(r0 + m + ck * M);
+            const int it = r0 + m + ck * M;
+            epilogue(it);
+            stored_after = SH == kPair && 2 * (it / a.nreg) + 1 >= a.F ? 0 : n_issued;
             clear();
             if (more)
                 read_step(nb, 0, X0);
