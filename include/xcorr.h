@@ -256,7 +256,8 @@ int xcorr_plan_tile(const xcorr_config *cfg, int32_t batch, int32_t *tile, int32
  * is reused once its previous ingest has finished), then ingested on
  * `compute_stream` after the copy; a device block (on_host = 0) is ingested
  * in place.  Every dump_every-th block the integration is dumped into d_out
- * (required on that push, *dumped = 1).  Two latencies are kept.  The service
+ * (required on that push, *dumped = 1), as by xcorr_ingest_dump where d_out is
+ * 16-byte aligned and blocks are not held in groups.  Two latencies are kept.  The service
  * time of each launch record (one block, or a held group), from the start of
  * its transfer (host blocks) or of its ingest (device blocks) to the end of
  * its ingest (and dump), comes from HIP events.  The block latency, per

@@ -194,3 +194,40 @@ def test_pipe_keeps_dropped_blocks_alive(host):
     assert np.array_equal(out.cpu().numpy(), oracle.to_int32(oracle.xcorr(v.numpy(), 4, nb * B, F, N)))
     p.close()
     c.close()
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("every", [1, 3])
+def test_pipe_dump_written_by_the_last_ingest(every, bits):
+    """The block that ends an integration writes the dump itself; whole
+    numbers, equal to the oracle.  A misaligned d_out is refused with the block
+    integrated, so a later dump holds it."""
+    N, F, B = 96, 3, 128
+    make = synth.uniform_volts4 if bits == 4 else synth.uniform_volts8
+    blocks = [make(N, F, B, seed=(4012, k)) for k in range(3 * every)]
+    c = X.Correlator(N, F, bits, X.PATH_I8_MFMA)
+    p = X.Pipe(c, B, every, host_blocks=False)
+    P = N * (N + 1) // 2
+    flat = torch.full((F * P * 2 + 4,), -1, dtype=torch.int32, device="cuda")
+    out = flat[:F * P * 2].view(F, P, 2)
+
+    def want(bs):
+        v = torch.cat(bs)
+        return oracle.to_int32(oracle.xcorr(v.numpy(), bits, v.shape[0], F, N))
+
+    for k, b in enumerate(blocks[:2 * every]):
+        if p.push(b.cuda(), out=out):
+            p.drain()
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), want(blocks[k - every + 1:k + 1])), k
+    assert (flat[F * P * 2:].cpu() == -1).all()
+    for b in blocks[2 * every:-1]:
+        p.push(b.cuda())
+    with pytest.raises(X.XcorrError):
+        p.push(blocks[-1].cuda(), out=flat[2:2 + F * P * 2].view(F, P, 2))
+    tail, n, _ = c.dump()
+    torch.cuda.synchronize()
+    assert n == every * B
+    assert np.array_equal(tail.cpu().numpy(), want(blocks[2 * every:]))
+    p.close()
+    c.close()
