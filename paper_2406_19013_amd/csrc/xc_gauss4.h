@@ -40,6 +40,8 @@
 #pragma once
 #include "xc_mfma4.h"
 
+#include <type_traits>
+
 namespace xc {
 namespace {
 
@@ -199,49 +201,6 @@ constexpr bool g3_owns_sums(int s, int b)
 {
     return kG3Split<D, SH>.sum_owner[b] == s;
 }
-// Order in which a wave unpacks its blocks within a K step: greedily the
-// block that completes the most MFMA work with the blocks already unpacked
-// (ties: the lower block), so that MFMAs start early and the later blocks'
-// unpacking runs under them.  pos < 0 for a block the wave does not read.
-template <int D, int SH>
-constexpr int g3_block_pos(int s, int b)
-{
-    constexpr int NB = g3_blocks<SH>(D);
-    if (!g3_uses_block<D, SH>(s, b))
-        return -1;
-    bool done[8] = {};
-    for (int p = 0; p < NB; ++p) {
-        int best = -1, best_gain = -1;
-        for (int c = 0; c < NB; ++c) {
-            if (done[c] || !g3_uses_block<D, SH>(s, c))
-                continue;
-            int gain = 0;
-            for (int t = 0; t < g3_tiles<SH>(D); ++t) {
-                const int r = g3_row<SH>(D, t), k = g3_col<SH>(D, t);
-                if (g3_has<D, SH>(s, t) && (r == c || k == c)) {
-                    const int o = r == c ? k : r;
-                    if (o == c || done[o])
-                        gain += g3_units<SH>(D, t);
-                }
-            }
-            if (gain > best_gain) {
-                best = c;
-                best_gain = gain;
-            }
-        }
-        if (best == b)
-            return p;
-        done[best] = true;
-    }
-    return -1;
-}
-// a tile's MFMAs go right after the later of its two blocks is unpacked
-template <int D, int SH>
-constexpr int g3_tile_pos(int s, int t)
-{
-    const int a = g3_block_pos<D, SH>(s, g3_row<SH>(D, t)), b = g3_block_pos<D, SH>(s, g3_col<SH>(D, t));
-    return a > b ? a : b;
-}
 template <int D, int SH>
 constexpr int g3_mfmas_of(int s)
 {
@@ -252,10 +211,38 @@ constexpr int g3_mfmas_of(int s)
     return n;
 }
 
+template <int D, int SH>
+constexpr int g3_nblocks_of(int s)
+{
+    int n = 0;
+    for (int b = 0; b < g3_blocks<SH>(D); ++b)
+        n += g3_uses_block<D, SH>(s, b);
+    return n;
+}
+template <int D, int SH>
+constexpr int g3_block_of(int s, int k)   // the k-th block slot s uses
+{
+    for (int b = 0;; ++b)
+        if (g3_uses_block<D, SH>(s, b) && k-- == 0)
+            return b;
+}
+// The k-th product of a slot's K step, in issue order: the tiles' A_i B_j,
+// their B_i A_j, their R_i R_j, so that products of one sum lie apart.
+struct G3Product { int tile, kind; };
+template <int D, int SH>
+constexpr G3Product g3_product(int s, int k)
+{
+    for (int kind = 0; kind < 3; ++kind)
+        for (int t = 0; t < g3_tiles<SH>(D); ++t)
+            if (g3_has<D, SH>(s, t) && !(kind == 1 && g3_isdiag<SH>(D, t)) && k-- == 0)
+                return {t, kind};
+    return {0, 0};
+}
+
 // rows of a tile's running sums that an accumulating epilogue requests ahead
 // of its stores: the whole tile where the registers allow, else half of it
 template <int SH>
-constexpr int g3_old_rows(int D) { return (SH == kTri && (D <= 3 || D == 6)) || (SH == kPair && D >= 4) ? 8 : 16; }
+constexpr int g3_old_rows(int D) { return SH == kTri ? (D <= 3 || D == 6 ? 4 : 16) : SH == kPair && D >= 4 ? 4 : 16; }
 
 // LDS transpose slot of a diagonal tile: its block
 template <int D, int SH>
@@ -305,6 +292,21 @@ __device__ __forceinline__ void wait_vmcnt_chunks_after(int r)
     } else {
         wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
     }
+}
+
+// A product, and an operand's unpacking, at their place in the source: the
+// empty statements keep the compiler from moving them past each other.
+__device__ __forceinline__ void mfma_in_order(v16i &acc, v4i a, v4i b)
+{
+    acc = mfma_i8(a, b, acc);
+    asm volatile("" : "+v"(acc));
+}
+__device__ __forceinline__ void unpack_in_order(int x, int &a, int &b, int &r)
+{
+    a = x ^ 0x08080808;
+    b = x ^ 0x07070707;
+    r = x & (int)0xF0F0F0F0;
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(r));
 }
 
 // LDS-only wait: outstanding LDS operations of this wave done, memory
@@ -642,52 +644,70 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
         }
     wait_vmcnt_chunks<LOADS, NBUF - 1>(n_issued - 1 - min(CPB - 1, total - 1));
     barrier_no_fence();
-    v4i X0[NB], X1[NB];    // packed operands of the current and the next K step
+    v4i X0[NB];                // packed operands of the next K step
     read_step(ring + row_off, 0, X0);
 
-    // one K step: unpack its operands and issue its MFMAs
-    // Dataflow order: unpack one block, then issue the MFMAs of the tiles
-    // that block completes, then the next block, whose unpack runs under
-    // those MFMAs; the scheduling groups at the end keep MFMAs and VALU work
-    // interleaved (one MFMA, then up to 6 VALU instructions).
+    v4i A[NB], B[NB], R[NB];   // the three forms of the current step
+    auto sums = [&](auto bc, auto kc) {
+        constexpr int b = bc, k = kc;
+        int &z = k & 1 ? sz2[b] : sz[b];
+        int &l = k & 1 ? sl2[b] : sl[b];
+        z = (int)__builtin_amdgcn_sad_u8((uint32_t)(A[b][k] ^ (int)0x80808080), 0u, (uint32_t)z);
+        l = (int)__builtin_amdgcn_sad_u8((uint32_t)A[b][k], (uint32_t)R[b][k], (uint32_t)l);
+    };
+    // A K step: its products, and between them the unpacking of the next one
+    // (in X) and its own sums.  The statements are pinned in this order: left
+    // to the compiler, a step's unpacking gathers before its first product,
+    // where the wave's matrix core is idle (192 inputs x 1024 channels x 4096
+    // samples 288 -> 276 us, 160 x 1024 x 2048 144 -> 137, 64 x 4096 x 2048
+    // 151 -> 138, a batch of four arrays 655 -> 635; three and four blocks
+    // 1 to 2 %: what is left is the power the products draw).
     auto step = [&](const v4i *X) {
-        v4i A[NB], B[NB], R[NB];
-        static_for<0, NB>([&](auto kc) {
-            constexpr int k = kc;
-            static_for<0, NB>([&](auto bc) {
-                constexpr int b = bc;
-                if constexpr (g3_block_pos<D, SH>(SLOT, b) == k) {
-                    A[b] = X[b] ^ 0x08080808;
-                    B[b] = X[b] ^ 0x07070707;
-                    R[b] = X[b] & (int)0xF0F0F0F0;
-                    if constexpr (g3_owns_sums<D, SH>(SLOT, b)) {
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            int &z = k & 1 ? sz2[b] : sz[b];
-                            int &l = k & 1 ? sl2[b] : sl[b];
-                            z = (int)__builtin_amdgcn_sad_u8((uint32_t)(A[b][k] ^ (int)0x80808080), 0u, (uint32_t)z);
-                            l = (int)__builtin_amdgcn_sad_u8((uint32_t)A[b][k], (uint32_t)R[b][k], (uint32_t)l);
-                        }
-                    }
-                }
+        constexpr int NM = g3_mfmas_of<D, SH>(SLOT), NBU = g3_nblocks_of<D, SH>(SLOT);
+        v4i An[NB], Bn[NB], Rn[NB];
+        static_for<0, NM>([&](auto kc) {
+            constexpr G3Product p = g3_product<D, SH>(SLOT, kc);
+            constexpr int q = g3_rank<D, SH>(SLOT, p.tile);
+            constexpr int I = g3_row<SH>(D, p.tile), J = g3_col<SH>(D, p.tile);
+            if constexpr (p.kind == 0)
+                mfma_in_order(acc_ab[q], A[I], B[J]);
+            else if constexpr (p.kind == 1)
+                mfma_in_order(acc_ba[q], B[I], A[J]);
+            else
+                mfma_in_order(acc_rr[q], R[I], R[J]);
+            static_for<kc * 4 * NBU / NM, (kc + 1) * 4 * NBU / NM>([&](auto u) {
+                constexpr int b = g3_block_of<D, SH>(SLOT, u % NBU), k = u / NBU;
+                int fa, fb, fr;
+                unpack_in_order(X[b][k], fa, fb, fr);
+                An[b][k] = fa;
+                Bn[b][k] = fb;
+                Rn[b][k] = fr;
+                if constexpr (g3_owns_sums<D, SH>(SLOT, b))
+                    sums(std::integral_constant<int, b>{}, std::integral_constant<int, k>{});
             });
-            static_for<0, NTT>([&](auto tc) {
-                constexpr int t = tc;
-                if constexpr (g3_has<D, SH>(SLOT, t) && g3_tile_pos<D, SH>(SLOT, t) == k) {
-                    constexpr int q = g3_rank<D, SH>(SLOT, t);
-                    constexpr int I = g3_row<SH>(D, t), J = g3_col<SH>(D, t);
-                    acc_ab[q] = mfma_i8(A[I], B[J], acc_ab[q]);
-                    if constexpr (!g3_isdiag<SH>(D, t))
-                        acc_ba[q] = mfma_i8(B[I], A[J], acc_ba[q]);
-                    acc_rr[q] = mfma_i8(R[I], R[J], acc_rr[q]);
-                }
-            });
+            __builtin_amdgcn_sched_barrier(0);
         });
-        static_for<0, g3_mfmas_of<D, SH>(SLOT)>([&](auto) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);   // up to six VALU
+        static_for<0, NB>([&](auto b) {
+            if constexpr (g3_uses_block<D, SH>(SLOT, b)) {
+                A[b] = An[b];
+                B[b] = Bn[b];
+                R[b] = Rn[b];
+            }
         });
     };
+    // the operands of a stream's or an item's first step (in X0) and the
+    // second step's packed ones
+    auto begin = [&](lds_u8 *p) {
+        static_for<0, NB>([&](auto b) {
+            if constexpr (g3_uses_block<D, SH>(SLOT, b)) {
+                A[b] = X0[b] ^ 0x08080808;
+                B[b] = X0[b] ^ 0x07070707;
+                R[b] = X0[b] & (int)0xF0F0F0F0;
+            }
+        });
+        read_step(p, 32 * kRowBytes, X0);
+    };
+    begin(ring + row_off);
 
     // Stores of the last epilogue and the number of chunks issued before it:
     // the wait for one of those chunks leaves the stores in flight.  (An item
@@ -697,11 +717,9 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
     int bufc = 0;          // ring slot of chunk gi
     int ck = 0, cc = 0;    // item, and chunk within the item, being computed
     for (int gi = 0; gi < total; ++gi) {
-        lds_u8 *const cb = ring + bufc * BUF + row_off;
         const int nbufc = bufc + 1 == NBUF ? 0 : bufc + 1;
-        // first K step of chunk gi; the second step's operands are read
+        // first K step of chunk gi; the second step's operands are unpacked
         // meanwhile
-        read_step(cb, 32 * kRowBytes, X1);
         step(X0);
         const bool more = gi + 1 < total;
         const bool item_end = cc + 1 == nch;
@@ -730,19 +748,24 @@ __device__ __forceinline__ void g3_wave(uint8_t *smem, const G3Args &a, const Bl
                 slot = slot + 1 == NBUF ? 0 : slot + 1;
             }
         }
-        // second K step of chunk gi, with the next chunk's first step read
-        // meanwhile unless an item ends here
+        // second K step of chunk gi, with the next chunk's first step read and
+        // unpacked meanwhile
         lds_u8 *const nb = ring + nbufc * BUF + row_off;
-        if (more && !item_end)
-            read_step(nb, 0, X0);
-        step(X1);
+        // (at an item's or the stream's end what is read and unpacked ahead
+        // is not used)
+        read_step(nb, 0, X0);
+        step(X0);
+        read_step(nb, 32 * kRowBytes, X0);
+        __builtin_amdgcn_sched_barrier(0);
         if (item_end) {
             const int it = r0 + m + ck * M;
             epilogue(it);
             stored_after = SH == kPair && 2 * (it / a.nreg) + 1 >= a.F ? 0 : n_issued;
             clear();
-            if (more)
+            if (more) {
                 read_step(nb, 0, X0);
+                begin(nb);
+            }
         }
         bufc = nbufc;
         if (item_end) {
