@@ -267,9 +267,12 @@ hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out,
     if (free_choice(ctx)) {
         if (word_rows(c, v)) {
             if (xc::gauss4_runs(ctx->plan, F, N)) {
-                const int rb = xc::split4_blocks(ctx->plan, F, N, T);
-                return rb ? xc::launch_split4(rb, v, T, F, N, out, accumulate, s, acc_in)
-                          : xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
+                const int2 *in = acc_in ? acc_in : out;
+                if (const int rb = xc::split4_blocks(ctx->plan, F, N, T))
+                    return xc::launch_split4(rb, v, T, F, N, out, accumulate, s, in);
+                if (xc::duo4_taken(N, T))
+                    return xc::launch_duo4(v, nullptr, T, F, N, out, in, accumulate, s);
+                return xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, in);
             }
         } else if (xc::split4_unaligned(F, N, T)) {
             return xc::launch_split4(1, v, T, F, N, out, accumulate, s, acc_in);
@@ -534,15 +537,16 @@ int xcorr_ingest_blocks(xcorr_ctx *ctx, const void *const *d_blocks, int n_block
         bt.chunks_per_block = (int)(block_samples / 64);
         const int accumulate = (ctx->acc_samples > 0 || b0 > 0) ? 1 : 0;
         const bool gauss = gauss_runs(ctx->k4, ctx->plan, c.n_chans, c.n_inputs);
-        const int rb = gauss && free_choice(ctx)
-                           ? xc::split4_blocks(ctx->plan, c.n_chans, c.n_inputs, n * block_samples) : 0;
-        const hipError_t e = rb ? xc::launch_split4_blocks(rb, bt, n, c.n_chans, c.n_inputs,
-                                                           static_cast<int2 *>(ctx->ws), accumulate, s)
-                             : gauss
-                                 ? xc::launch_gauss4_blocks(ctx->plan, bt, n, c.n_chans, c.n_inputs,
-                                                            static_cast<int2 *>(ctx->ws), accumulate, s)
-                                 : xc::launch_mfma4f_blocks(ctx->plan, bt, n, c.n_chans, c.n_inputs,
-                                                            static_cast<int2 *>(ctx->ws), accumulate, s);
+        const bool choose = gauss && free_choice(ctx);
+        const int F = c.n_chans, N = c.n_inputs;
+        const int64_t T = n * block_samples;
+        int2 *const acc = static_cast<int2 *>(ctx->ws);
+        const int rb = choose ? xc::split4_blocks(ctx->plan, F, N, T) : 0;
+        const hipError_t e =
+            rb                               ? xc::launch_split4_blocks(rb, bt, n, F, N, acc, accumulate, s)
+            : choose && xc::duo4_taken(N, T) ? xc::launch_duo4(bt.p[0], &bt, T, F, N, acc, acc, accumulate, s)
+            : gauss                          ? xc::launch_gauss4_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s)
+                                             : xc::launch_mfma4f_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
         ++ctx->launches;

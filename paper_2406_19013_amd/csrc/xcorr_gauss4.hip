@@ -32,28 +32,12 @@ void xc_gauss4_kernel(const G3Args a, const BlockTable bt)
     g3_dispatch<D, SH, ACC, MB>(smem, a, &bt);
 }
 
-// compute units of the current device (queried once per device)
-int device_cu_count()
-{
-    static int cached[64] = {0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
-        return 256;
-    if (!cached[dev]) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-            cus = 256;
-        cached[dev] = cus;
-    }
-    return cached[dev];
-}
-
 template <int D, int SH>
 hipError_t launch_shape(const G3Args &a, const BlockTable *bt, int accumulate, hipStream_t s)
 {
     const int64_t items = g3_items<SH>(a.F, a.nreg);
     const int per = (int)((items + 7) / 8);
-    const int m_max = device_cu_count() * g3_wgs_per_cu<SH>(D) / 8;
+    const int m_max = compute_units() * g3_wgs_per_cu<SH>(D) / 8;
     const int grid = 8 * std::max(1, std::min(m_max, per));
     G3Args args = a;
     args.per = per;

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include "xcorr.h"
+#include <atomic>
 #include <cstdint>
 #include <string>
 
@@ -44,6 +45,22 @@ int correlate_once(const xcorr_config *cfg, void *ws, size_t ws_bytes, const voi
 // 4+4-bit: the fused-product kernel keeps two K-parity partial sums of at
 // most 32896 per sample each (|256 Im| + |16 re|), over 32-sample steps, so a
 // launch takes at most 2 * 32 * floor((2^31 - 1) / 32896 / 32) samples.
+// compute units of the current device (queried once per device)
+inline int compute_units()
+{
+    static std::atomic<int> cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64)
+        return 256;
+    int cus = cached[dev].load(std::memory_order_relaxed);
+    if (!cus) {
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
+            cus = 256;
+        cached[dev].store(cus, std::memory_order_relaxed);
+    }
+    return cus;
+}
+
 constexpr int64_t kMaxSamplesPerLaunch4 = 130560;
 
 constexpr int64_t kMaxSamplesPerLaunch8 = 133143;  // |re*re| <= 127^2 per sample
@@ -123,6 +140,14 @@ hipError_t launch_split8(int rb, bool f16, const uint8_t *volts, int64_t T, int 
                          const void *acc_in, int accumulate, hipStream_t s);
 hipError_t launch_split4_blocks(int rb, const BlockTable &bt, int n_blocks, int F, int N, int2 *acc, int accumulate,
                                 hipStream_t s);
+
+// 4+4-bit kernel for segments of 128 inputs, two work-groups per compute unit
+// (rows on 4-byte boundaries; with a block table, blocks of 64-sample chunks),
+// and the rule that takes it.
+constexpr int64_t kMaxSamplesDuo4 = 65472;   // int32 accumulators of 2^15 per sample
+bool duo4_taken(int N, int64_t T);
+hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
+                       int accumulate, hipStream_t s);
 
 // Batched launch (4+4-bit, int8 MFMA) over up to kMaxBatchArrays arrays of
 // uneven N, F and sample counts; the descriptors travel by value in the kernel

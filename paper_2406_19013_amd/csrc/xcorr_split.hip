@@ -508,12 +508,13 @@ bool split_words(const void *volts, int F, int N, int bps)
 // work-groups, each walking every sample; this one pays per work-group (512 at
 // a time for regions of one block, 256 for two) plus a part that shrinks with
 // the load.  Measured on both sides of the line (this kernel against the
-// other): 4+4-bit, 192 inputs x 4096 samples: 32 channels 20.8 and 55 us, 64
-// channels 37 and 57, 128 channels 55 and 58, 256 channels 109 and 69; 64
-// inputs x 8192: 256 channels 29 and 69, 1024 channels 155 and 138; 8+8-bit,
-// 192 inputs x 8192: 32 channels 45 and 147 (FP16 68 and 272), 128 channels
-// 149 and 150 (200 and 276); 128 inputs x 512 channels x 8192: 311 and 238
-// (387 and 385).  It is taken only where the estimate is 10 % better.
+// other): 4+4-bit, 192 inputs: 32 channels x 4096 samples 19 and 48 us, 64 x
+// 2048 25 and 29, 128 x 1024 26 and 21; 128 inputs: 64 x 4096 20 and 31, 128 x
+// 1024 15 and 12; 256 x 64 x 1024 24 and 30; 384 x 64 x 1024 47 and 34; 512 x 16
+// x 2048 33 and 49; 64 inputs x 8192: 256 channels 29 and 69, 1024 channels 155
+// and 138; 8+8-bit, 192 inputs x 8192: 32 channels 45 and 147 (FP16 68 and 272),
+// 128 channels 149 and 150 (200 and 276); 128 inputs x 512 channels x 8192: 311
+// and 238 (387 and 385).  It is taken only where the estimate is 10 % better.
 namespace {
 struct SplitCost {
     double one, one_load, two;                   // per sample: one-block regions (base, per load), two-block ones
@@ -521,10 +522,11 @@ struct SplitCost {
     double chunk2, chunk3, chunk4, chunk6, rect_chunk;   // and its time per sample
     bool pairs;                                  // triangles of 2 to 4 blocks go two channels to an item
     bool one_launch;                             // triangles and rectangles fill rounds together
+    bool four_bit;                               // arrays that the kernels for 129 .. 192 inputs and for 128-input segments take
 };
-constexpr SplitCost kCost4{0.001, 0.0037, 0.0034, 3.5, 4.5, 7.0, 7.0, 7.0, 0.0078, 0.0088, 0.0117, 0.0117, 0.0117, true, false};
-constexpr SplitCost kCost8{0.0015, 0.0062, 0.0052, 2.5, 4.0, 5.0, 9.5, 7.0, 0.0063, 0.0083, 0.0105, 0.0170, 0.0140, false, true};
-constexpr SplitCost kCost8H{0.0026, 0.006, 0.0072, 3.0, 4.5, 5.0, 9.5, 8.0, 0.0102, 0.0152, 0.0195, 0.0317, 0.0312, false, true};
+constexpr SplitCost kCost4{0.001, 0.0037, 0.0034, 3.5, 4.5, 7.0, 7.0, 7.0, 0.0078, 0.0088, 0.0117, 0.0117, 0.0117, true, false, true};
+constexpr SplitCost kCost8{0.0015, 0.0062, 0.0052, 2.5, 4.0, 5.0, 9.5, 7.0, 0.0063, 0.0083, 0.0105, 0.0170, 0.0140, false, true, false};
+constexpr SplitCost kCost8H{0.0026, 0.006, 0.0072, 3.0, 4.5, 5.0, 9.5, 8.0, 0.0102, 0.0152, 0.0195, 0.0317, 0.0312, false, true, false};
 
 int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
 {
@@ -543,7 +545,14 @@ int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
     const bool pairs = c.pairs && pl.D >= 2 && pl.D <= 4 && F >= 2;
     const double tri_items = (pairs ? (F + 1) / 2 : F) * (double)pl.nseg, rect_items = F * (double)(pl.regions - pl.nseg);
     double other;
-    if (c.one_launch && pl.nseg > 1)
+    if (c.four_bit && duo4_taken(N, T)) {
+        // two work-groups per compute unit: below half a load a round takes
+        // its least time; results are written at about 5 TB/s
+        const double nseg = (N + 127) / 128, tri = F * nseg, rect = tri * (nseg - 1) / 2;
+        other = 4.5 + t * std::max(0.0068, 0.0168 * tri / 512.0) + 0.0132 * tri;
+        if (rect > 0)
+            other += 5.7 + t * std::max(0.0115, 0.0185 * rect / 512.0) + 0.026 * rect;
+    } else if (c.one_launch && pl.nseg > 1)
         other = std::ceil((tri_items + rect_items) / 256.0) * (c.rect_fixed + c.rect_chunk * t);
     else
         other = std::ceil(tri_items / 256.0) * (fixed + chunk * t) + std::ceil(rect_items / 256.0) * (c.rect_fixed + c.rect_chunk * t);
