@@ -33,7 +33,7 @@ UNITS = [("xcorr_kernels.hip", [], "xcorr_kernels.o"), ("xcorr_api.cpp", [], "xc
          ("xcorr_mfma4.hip", [], "xcorr_mfma4.o"), ("xcorr_mfma4f.hip", [], "xcorr_mfma4f.o"),
          ("xcorr_batch.hip", [], "xcorr_batch.o"),
          ("xcorr_gauss4.hip", [], "xcorr_gauss4.o"), ("xcorr_gauss4_batch.hip", [], "xcorr_gauss4_batch.o"),
-         ("xcorr_split.hip", [], "xcorr_split.o"), ("xcorr_duo4.hip", [], "xcorr_duo4.o"),
+         ("xcorr_split.hip", [], "xcorr_split.o"), ("xcorr_duo4.hip", [], "xcorr_duo4.o"), ("xcorr_tri48.hip", [], "xcorr_tri48.o"),
          ("xcorr_static.hip", [], "xcorr_static.o"),
          ("xcorr_ceiling.hip", [], "xcorr_ceiling.o"),
          ("xcorr_fengine.hip", [], "xcorr_fengine.o"),

@@ -124,6 +124,15 @@ __device__ __forceinline__ void wait_vmcnt_chunks(int r)
     }
 }
 
+// The same pointer, in scalar registers: a buffer descriptor that the compiler
+// holds in vector registers costs a loop around every access.
+__device__ __forceinline__ const uint8_t *uniform_pointer(const uint8_t *p)
+{
+    const uint64_t u = (uint64_t)p;
+    return (const uint8_t *)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32 |
+                             (uint32_t)__builtin_amdgcn_readfirstlane((int)u));
+}
+
 constexpr int kBufferOutOfRange = (int)0xFFFFFFF0;  // any offset >= num_records reads 0
 
 // Cache policy of the LDS-DMA input loads (sc0 | nt | sc1): every input byte

@@ -272,6 +272,8 @@ hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out,
                     return xc::launch_split4(rb, v, T, F, N, out, accumulate, s, in);
                 if (xc::duo4_taken(N, T))
                     return xc::launch_duo4(v, nullptr, T, F, N, out, in, accumulate, s);
+                if (xc::tri48_taken(N))
+                    return xc::launch_tri48(v, nullptr, T, F, N, out, in, accumulate, s);
                 return xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, in);
             }
         } else if (xc::split4_unaligned(F, N, T)) {
@@ -545,6 +547,7 @@ int xcorr_ingest_blocks(xcorr_ctx *ctx, const void *const *d_blocks, int n_block
         const hipError_t e =
             rb                               ? xc::launch_split4_blocks(rb, bt, n, F, N, acc, accumulate, s)
             : choose && xc::duo4_taken(N, T) ? xc::launch_duo4(bt.p[0], &bt, T, F, N, acc, acc, accumulate, s)
+            : choose && xc::tri48_taken(N)   ? xc::launch_tri48(bt.p[0], &bt, T, F, N, acc, acc, accumulate, s)
             : gauss                          ? xc::launch_gauss4_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s)
                                              : xc::launch_mfma4f_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s);
         if (e != hipSuccess)

@@ -149,6 +149,12 @@ bool duo4_taken(int N, int64_t T);
 hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                        int accumulate, hipStream_t s);
 
+// 4+4-bit kernel for one triangle of 129 to 192 inputs, as four segments of
+// 48 (same operands), and its rule.
+bool tri48_taken(int N);
+hipError_t launch_tri48(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
+                        int accumulate, hipStream_t s);
+
 // Batched launch (4+4-bit, int8 MFMA) over up to kMaxBatchArrays arrays of
 // uneven N, F and sample counts; the descriptors travel by value in the kernel
 // arguments, so a captured graph holds everything it needs.  The queue-driven

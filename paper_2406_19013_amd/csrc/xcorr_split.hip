@@ -552,6 +552,8 @@ int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
         other = 4.5 + t * std::max(0.0068, 0.0168 * tri / 512.0) + 0.0132 * tri;
         if (rect > 0)
             other += 5.7 + t * std::max(0.0115, 0.0185 * rect / 512.0) + 0.026 * rect;
+    } else if (c.four_bit && tri48_taken(N)) {
+        other = std::ceil(F / 256.0) * (6.0 + 0.0105 * t);
     } else if (c.one_launch && pl.nseg > 1)
         other = std::ceil((tri_items + rect_items) / 256.0) * (c.rect_fixed + c.rect_chunk * t);
     else
