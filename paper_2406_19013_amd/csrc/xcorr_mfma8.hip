@@ -24,9 +24,10 @@ namespace {
 // 2^11, so the FP16 operands are exact; FP32 accumulation rounds only once a
 // partial sum passes 2^24.
 //
-// Eight waves per work-group: product (Re, Im) x K parity x tile half.  Wave w
-// sits on SIMD w mod 4 = (product, parity), so each SIMD carries one product
-// over every other 16-sample K step for all tiles of the region.
+// Eight waves per work-group: product (Re, Im) x K parity x tile half.  The two
+// waves of a SIMD (w and w + 4) carry the Re and the Im product of one parity
+// and different halves, since the Im product's column operands take more
+// vector instructions.
 //
 // LDS: time rows of 512 bytes = 32 units of 16 bytes (unit p = inputs
 // 8p..8p+7 of the region's staged blocks, 4 units per 32-input block); unit p
@@ -55,21 +56,22 @@ __device__ __forceinline__ int swap_not(int x)
     return (int)__builtin_amdgcn_perm((unsigned)x, (unsigned)x, 0x02030001u) ^ 0x00FF00FF;
 }
 
-// two int8 (re, im) pairs (one dword) -> two half2 (re, im), exact
-__device__ __forceinline__ void pairs_to_f16(int x, int &h0, int &h1)
+// FP16 operands, exact: t holds a byte b as b + 128, whose half is 1152 + b
+// with 0x64 above it; a pair's halves less 1152 are (re, im), and exchanged
+// with the sign of the first turned, (-im, re): one packed add each.
+__device__ __forceinline__ v2h pair_f16(unsigned t, int e)
 {
-    const unsigned t = (unsigned)x ^ 0x80808080u;               // b + 128
-    const unsigned a = __builtin_amdgcn_perm(0x64646464u, t, 0x04010400u);
-    const unsigned b = __builtin_amdgcn_perm(0x64646464u, t, 0x04030402u);
-    const v2h off = {(_Float16)-1152.0f, (_Float16)-1152.0f};  // 1024 + 128
-    h0 = __builtin_bit_cast(int, __builtin_bit_cast(v2h, a) + off);
-    h1 = __builtin_bit_cast(int, __builtin_bit_cast(v2h, b) + off);
+    return __builtin_bit_cast(v2h, __builtin_amdgcn_perm(0x64646464u, t, e ? 0x04030402u : 0x04010400u));
 }
-
-// half2 (re, im) -> (-im, re)
-__device__ __forceinline__ int neg_swap_f16(int h)
+__device__ __forceinline__ int row_f16(v2h a)
 {
-    return (int)__builtin_amdgcn_alignbit((unsigned)h, (unsigned)h, 16) ^ 0x00008000;
+    const v2h off = {(_Float16)-1152.0f, (_Float16)-1152.0f};
+    return __builtin_bit_cast(int, a + off);
+}
+__device__ __forceinline__ int col_f16(v2h a)
+{
+    const v2h off = {(_Float16)1152.0f, (_Float16)-1152.0f};
+    return __builtin_bit_cast(int, v2h{-a.y, a.x} + off);
 }
 
 constexpr int role8(int prod, int par) { return prod + 2 * par; }
@@ -82,69 +84,158 @@ constexpr bool half_owns_rowsum(int D, bool tri, int half, int I)
     return (t >= half_begin(D, tri, half)) && (t < half_end(D, tri, half));
 }
 
-template <int D, bool TRI, bool F16, int PROD, int HALF, int KOFF>
-__device__ __forceinline__ void k_step8(lds_u8 *const *addr, typename std::conditional<F16, v16f, v16i>::type *acc,
-                                        int *rsum)
+template <int D, bool TRI, int PROD, int HALF, int KOFF>
+__device__ __forceinline__ void k_step8(lds_u8 *const *addr, v16i *acc, int *rsum)
 {
     constexpr int NB = TRI ? D : 2 * D;
     constexpr int T0 = half_begin(D, TRI, HALF), T1 = half_end(D, TRI, HALF);
-    if constexpr (!F16) {
-        v4i A[NB], B[NB];
-        static_for<0, NB>([&](auto bc) {
-            constexpr int b = bc;
-            constexpr bool ua = half_uses_row(D, TRI, HALF, b), ub = half_uses_col(D, TRI, HALF, b);
-            if constexpr (ua || ub) {
-                const v2i lo = tr16(addr[b] + KOFF);
-                const v2i hi = tr16(addr[b] + KOFF + 4 * kRow8);
-                const v4i x = v4i{lo.x, lo.y, hi.x, hi.y};
-                if constexpr (ua) {
-                    A[b] = x;
-                    if constexpr (PROD == 1 && b < D && half_owns_rowsum(D, TRI, HALF, b))
-                        for (int k = 0; k < 4; ++k)
-                            rsum[b] = __builtin_amdgcn_sdot4(x[k], 0x00010001, rsum[b], false);
-                }
-                if constexpr (ub) {
-                    if constexpr (PROD == 0)
-                        B[b] = x;
-                    else
-                        B[b] = v4i{swap_not(x.x), swap_not(x.y), swap_not(x.z), swap_not(x.w)};
-                }
+    v4i A[NB], B[NB];
+    static_for<0, NB>([&](auto bc) {
+        constexpr int b = bc;
+        constexpr bool ua = half_uses_row(D, TRI, HALF, b), ub = half_uses_col(D, TRI, HALF, b);
+        if constexpr (ua || ub) {
+            const v2i lo = tr16(addr[b] + KOFF);
+            const v2i hi = tr16(addr[b] + KOFF + 4 * kRow8);
+            const v4i x = v4i{lo.x, lo.y, hi.x, hi.y};
+            if constexpr (ua) {
+                A[b] = x;
+                if constexpr (PROD == 1 && b < D && half_owns_rowsum(D, TRI, HALF, b))
+                    for (int k = 0; k < 4; ++k)
+                        rsum[b] = __builtin_amdgcn_sdot4(x[k], 0x00010001, rsum[b], false);
+            }
+            if constexpr (ub) {
+                if constexpr (PROD == 0)
+                    B[b] = x;
+                else
+                    B[b] = v4i{swap_not(x.x), swap_not(x.y), swap_not(x.z), swap_not(x.w)};
+            }
+        }
+    });
+    static_for<T0, T1>([&](auto tc) {
+        constexpr int t = tc;
+        acc[t - T0] = mfma_i8(A[row_block(D, TRI, t)], B[col_block(D, TRI, t)], acc[t - T0]);
+    });
+}
+
+// FP16 path: the order in which a wave converts its blocks, each time the one
+// that completes the most tiles with those before it, and those tiles.
+struct F16Order {
+    int n = 0;
+    int block[12] = {}, ntiles[12] = {}, tile[12][12] = {};
+};
+constexpr F16Order f16_order(int D, bool tri, int half)
+{
+    F16Order o;
+    bool used[12] = {}, done[12] = {};
+    const int t0 = half_begin(D, tri, half), t1 = half_end(D, tri, half);
+    int row[21] = {}, col[21] = {};
+    for (int t = t0; t < t1; ++t) {
+        row[t - t0] = row_block(D, tri, t);
+        col[t - t0] = col_block(D, tri, t);
+        used[row[t - t0]] = used[col[t - t0]] = true;
+    }
+    for (int b = 0; b < 12; ++b)
+        o.n += used[b];
+    for (int k = 0; k < o.n; ++k) {
+        int best = -1, best_gain = -1;
+        for (int c = 0; c < 12; ++c) {
+            if (!used[c] || done[c])
+                continue;
+            int gain = 0;
+            for (int t = 0; t < t1 - t0; ++t)
+                gain += (row[t] == c || col[t] == c) && (row[t] == c || done[row[t]]) && (col[t] == c || done[col[t]]);
+            if (gain > best_gain) {
+                best = c;
+                best_gain = gain;
+            }
+        }
+        o.block[k] = best;
+        for (int t = 0; t < t1 - t0; ++t)
+            if ((row[t] == best || col[t] == best) && (row[t] == best || done[row[t]]) &&
+                (col[t] == best || done[col[t]]))
+                o.tile[k][o.ntiles[k]++] = t0 + t;
+        done[best] = true;
+    }
+    return o;
+}
+template <int D, bool TRI, int HALF>
+constexpr F16Order kF16Order = f16_order(D, TRI, HALF);
+
+// The K steps of one chunk on the FP16 path: STEPS steps of 8 samples, the
+// first two at rows 16 PAR of the chunk, the next two 32 rows on.  While the
+// products that a block completes run, the next block is converted, the next
+// step's first one at the end; the statements are pinned in this order, and
+// the operands of a step are read from LDS as the previous step's are
+// converted.  What bounds the path is the issue of products and conversions:
+// one product hides about 5 vector instructions, and a wave issues 4 to 6 (5
+// per dword and form, 2 where a block is both row and column; it was 6 to 10
+// on the SIMDs of the Im product, all ahead of the first product).  192 inputs
+// x 512 channels x 8192 samples: 672 -> 609 us, and 585 with the waves'
+// priorities; 128 x 512 x 4096 218 -> 180; 256 x 256 x 2048 242 -> 182.
+template <int D, bool TRI, int PROD, int HALF, int PAR, int STEPS>
+__device__ __forceinline__ void chunk_f16(lds_u8 *const *addr, v16f *acc)
+{
+    constexpr int NB = TRI ? D : 2 * D, T0 = half_begin(D, TRI, HALF);
+    constexpr F16Order O = kF16Order<D, TRI, HALF>;
+    constexpr int NBU = O.n;
+    v2i X[NB];
+    v4i A[NB], B[NB], An, Bn;
+    unsigned t = 0;
+    auto read = [&](auto bc, auto sc) {
+        constexpr int b = bc, s = sc;
+        X[b] = tr16(addr[b] + (16 * (PAR + 2 * (s / 2)) + 8 * (s % 2)) * kRow8);
+    };
+    auto convert = [&](auto bc, auto ec, v4i &fa, v4i &fb) {   // samples' pair e of a block
+        constexpr int b = bc, e = ec;
+        if constexpr (e % 2 == 0)
+            t = (unsigned)X[b][e / 2] ^ 0x80808080u;            // b + 128
+        const v2h p = pair_f16(t, e % 2);
+        if constexpr (half_uses_row(D, TRI, HALF, b) || PROD == 0) {
+            int h = row_f16(p);
+            asm volatile("" : "+v"(h));
+            fa[e] = h;
+        }
+        if constexpr (half_uses_col(D, TRI, HALF, b) && PROD == 1) {
+            int h = col_f16(p);
+            asm volatile("" : "+v"(h));
+            fb[e] = h;
+        }
+    };
+    static_for<0, NBU>([&](auto k) {
+        read(std::integral_constant<int, O.block[k]>{}, std::integral_constant<int, 0>{});
+    });
+    constexpr int first = O.block[0];
+    static_for<0, 4>([&](auto e) { convert(std::integral_constant<int, first>{}, e, A[first], B[first]); });
+    static_for<0, STEPS>([&](auto sc) {
+        // waves lower their priority as they pass through the chunk, so that
+        // the one behind on a SIMD catches up before the barrier
+        __builtin_amdgcn_s_setprio(sc < 3 ? 3 - sc : 0);
+        static_for<0, NBU>([&](auto kc) {
+            constexpr int s = sc, k = kc, NM = O.ntiles[k];
+            constexpr bool wrap = k + 1 == NBU, work = !wrap || s + 1 < STEPS;
+            constexpr int b = O.block[wrap ? 0 : k + 1];
+            if constexpr (s + 1 < STEPS)
+                read(std::integral_constant<int, O.block[k]>{}, std::integral_constant<int, s + 1>{});
+            v4i &fa = wrap ? An : A[b], &fb = wrap ? Bn : B[b];
+            static_for<0, NM>([&](auto nc) {
+                constexpr int tile = O.tile[k][nc], i = row_block(D, TRI, tile), j = col_block(D, TRI, tile);
+                acc[tile - T0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                    __builtin_bit_cast(v8h, A[i]), __builtin_bit_cast(v8h, PROD == 0 ? A[j] : B[j]), acc[tile - T0], 0, 0, 0);
+                asm volatile("" : "+v"(acc[tile - T0]));
+                if constexpr (work)
+                    static_for<nc * 4 / NM, (nc + 1) * 4 / NM>([&](auto e) {
+                        convert(std::integral_constant<int, b>{}, e, fa, fb);
+                    });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (NM == 0 && work)
+                static_for<0, 4>([&](auto e) { convert(std::integral_constant<int, b>{}, e, fa, fb); });
+            if constexpr (wrap && work) {
+                A[b] = An;
+                B[b] = Bn;
             }
         });
-        static_for<T0, T1>([&](auto tc) {
-            constexpr int t = tc;
-            acc[t - T0] = mfma_i8(A[row_block(D, TRI, t)], B[col_block(D, TRI, t)], acc[t - T0]);
-        });
-    } else {
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            v8h A[NB], B[NB];
-            static_for<0, NB>([&](auto bc) {
-                constexpr int b = bc;
-                constexpr bool ua = half_uses_row(D, TRI, HALF, b), ub = half_uses_col(D, TRI, HALF, b);
-                if constexpr (ua || ub) {
-                    const v2i x = tr16(addr[b] + KOFF + m * 8 * kRow8);
-                    int h[4];
-                    pairs_to_f16(x.x, h[0], h[1]);
-                    pairs_to_f16(x.y, h[2], h[3]);
-                    if constexpr (ua)
-                        A[b] = __builtin_bit_cast(v8h, v4i{h[0], h[1], h[2], h[3]});
-                    if constexpr (ub) {
-                        if constexpr (PROD == 0)
-                            B[b] = __builtin_bit_cast(v8h, v4i{h[0], h[1], h[2], h[3]});
-                        else
-                            B[b] = __builtin_bit_cast(v8h, v4i{neg_swap_f16(h[0]), neg_swap_f16(h[1]),
-                                                               neg_swap_f16(h[2]), neg_swap_f16(h[3])});
-                    }
-                }
-            });
-            static_for<T0, T1>([&](auto tc) {
-                constexpr int t = tc;
-                acc[t - T0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[row_block(D, TRI, t)],
-                                                                    B[col_block(D, TRI, t)], acc[t - T0], 0, 0, 0);
-            });
-        }
-    }
+    });
 }
 
 constexpr int mfma8_nbuf() { return 4; }
@@ -174,7 +265,7 @@ __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__res
     static_assert(KC % 32 == 0, "a chunk holds whole pairs of 16-sample K steps");
 
     const int lane = threadIdx.x & 63;
-    constexpr int WAVE = PROD + 2 * PAR + 4 * HALF;   // the wave that runs this role
+    constexpr int WAVE = (PROD ^ HALF) + 2 * PAR + 4 * HALF;   // the wave that runs this role
     const int g = lane >> 4, q = lane & 15;
     lds_u8 *const ring = (lds_u8 *)smem;
 
@@ -245,9 +336,13 @@ __device__ __forceinline__ void mfma8_region(uint8_t *smem, const uint8_t *__res
         for (int b = 0; b < NB; ++b)
             addr[b] = cb + colo[b];
         // 16-sample K steps of this chunk: this wave takes those of its parity
-        k_step8<D, TRI, F16, PROD, HALF, PAR * 16 * kRow8>(addr, acc, rsum);
-        if constexpr (KC == 64)
-            k_step8<D, TRI, F16, PROD, HALF, (PAR + 2) * 16 * kRow8>(addr, acc, rsum);
+        if constexpr (F16) {
+            chunk_f16<D, TRI, PROD, HALF, PAR, KC / 16>(addr, acc);
+        } else {
+            k_step8<D, TRI, PROD, HALF, PAR * 16 * kRow8>(addr, acc, rsum);
+            if constexpr (KC == 64)
+                k_step8<D, TRI, PROD, HALF, (PAR + 2) * 16 * kRow8>(addr, acc, rsum);
+        }
     };
 
     int bufc = 0;
@@ -404,7 +499,7 @@ __device__ __forceinline__ void mfma8_dispatch(uint8_t *smem, const uint8_t *__r
     switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
 #define XC_CASE8(W)                                                                                     \
     case W:                                                                                             \
-        mfma8_region<D, TRI, F16, KC, NBUF, VEC, ((W) & 1), (((W) >> 1) & 1), ((W) >> 2)>(            \
+        mfma8_region<D, TRI, F16, KC, NBUF, VEC, (((W) ^ ((W) >> 2)) & 1), (((W) >> 1) & 1), ((W) >> 2)>( \
             smem, volts, T, F, N, f, row_blk, col_blk, acc_out, acc_in, accumulate);                    \
         break;
         XC_CASE8(0) XC_CASE8(1) XC_CASE8(2) XC_CASE8(3) XC_CASE8(4) XC_CASE8(5) XC_CASE8(6) XC_CASE8(7)
