@@ -24,8 +24,8 @@
 // samples, 1.2 GB: 292 -> 260 us, 4.7 TB/s); for rectangles the power that the
 // products draw, then each segment's samples being read once per pair of
 // segments.  Against the three-product kernel: 512 inputs x 512 channels x 2048
-// samples 570 -> 496 us; 256 x 512 x 2048 162 -> 146; 200 x 512 x 2000 152 ->
-// 131; 1024 x 64 x 2048 267 -> 230; 128 x 256 x 4096 60 -> 37 (that kernel
+// samples 570 -> 486 us; 256 x 512 x 2048 162 -> 137; 200 x 512 x 2000 152 ->
+// 125; 1024 x 64 x 2048 267 -> 228; 128 x 256 x 4096 60 -> 37 (that kernel
 // takes channels in pairs, which leaves half the chip idle).
 #include "xc_mfma4.h"
 
@@ -106,8 +106,7 @@ constexpr DuoProduct duo_product(int SH, int ROLE, int k)
 struct DuoArgs {
     int64_t T;        // samples (MB = 1: whole blocks)
     int F, N;
-    int nreg;         // regions of this launch's shape per channel
-    int per;          // items (channel, region) per XCD range
+    int ntri, nrect;  // triangles and rectangles per channel
     int2 *out;        // [F][P] results
     const int2 *in;   // [F][P] running sums (ACC = 1)
 };
@@ -147,20 +146,20 @@ __device__ __forceinline__ void unpack_in_order(int x, v4i &re, v4i &im, int e)
 
 template <int SH, int ROLE, int ACC, int MB>
 __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const BlockTable &bt,
-                                         const uint8_t *__restrict__ volts, int wave)
+                                         const uint8_t *__restrict__ volts, int wave, int nreg)
 {
     constexpr int NB = duo_blocks(SH), ROW = duo_row_bytes(SH), SLOT = duo_slot_bytes(SH), NBUF = duo_nbuf(SH);
     constexpr int C = duo_rows(SH), STEPS = C / 32;
     constexpr int U = 2 * NB;                             // 16-byte units per row
     constexpr int LOADS = SLOT / 1024 / kDuoWaves;            // loads per wave and chunk
     constexpr int NT = duo_ntiles(SH, ROLE);
-    const int lane = threadIdx.x & 63;
+    const int lane = __lane_id();
     const int g = lane >> 4, q = lane & 15;
     lds_u8 *const ring = (lds_u8 *)smem;
 
     const int xcd = blockIdx.x & 7, m = (int)(blockIdx.x >> 3), M = gridDim.x >> 3;
-    const int first = xcd * a.per;
-    const int rlen = min(a.per, a.F * a.nreg - first);
+    const int per = (a.F * nreg + 7) / 8, first = xcd * per;   // this XCD's items (channel, region)
+    const int rlen = min(per, a.F * nreg - first);
     const int n_my = rlen > m ? (rlen - m + M - 1) / M : 0;
     const int nch = (int)((a.T + C - 1) / C);
     const int total = n_my * nch;
@@ -189,10 +188,10 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     int is_k = 0, is_c = 0, issued = 0, islot = 0;
     int voff[LOADS];
     auto set_item = [&](int k) {
-        const int it = first + m + k * M, f = it / a.nreg;
+        const int it = first + m + k * M, f = it / nreg;
         int sa, sb;
-        segments(it - f * a.nreg, sa, sb);
-        int ln = lane;                        // recomputed per item: kept, these values would take
+        segments(it - f * nreg, sa, sb);
+        int ln = __lane_id();                 // recomputed per item: kept, these values would take
         asm volatile("" : "+v"(ln));          // the K loop's registers
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
@@ -318,9 +317,9 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     };
 
     auto epilogue = [&](int it) {
-        const int f = __builtin_amdgcn_readfirstlane(it / a.nreg);
+        const int f = __builtin_amdgcn_readfirstlane(it / nreg);
         int sa, sb;
-        segments(it - f * a.nreg, sa, sb);
+        segments(it - f * nreg, sa, sb);
         const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
         const int bytes = (int)(8 * P);
         // rows past input N - 1 lie past the end of the channel's triangle:
@@ -329,7 +328,7 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
             __builtin_amdgcn_make_buffer_rsrc((void *)(a.out + f * P), (short)0, bytes, 0x00020000);
         __amdgpu_buffer_rsrc_t in_f =
             __builtin_amdgcn_make_buffer_rsrc((void *)(a.in + f * P), (short)0, bytes, 0x00020000);
-        int ln = lane;                        // as in set_item
+        int ln = __lane_id();                 // as in set_item
         asm volatile("" : "+v"(ln));
         const int jl = ln & 31, il0 = 4 * (ln >> 5);
         static_for<0, NT>([&](auto tc) {
@@ -343,7 +342,7 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
                 return diag && j > i + u ? kBufferOutOfRange : off;
             };
             // running sums, OR rows at a time (registers)
-            constexpr int OR = SH == kDuoRect ? 8 : 16;
+            constexpr int OR = SH == kDuoRect ? 4 : 16;
             v2i old[ACC ? OR : 1];
             auto load_old = [&](int r0) {
 #pragma unroll
@@ -486,33 +485,42 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
 }
 
 template <int SH, int ACC, int MB>
-__global__ __launch_bounds__(kDuoThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void xc_duo4_kernel(const uint8_t *__restrict__ volts, const DuoArgs a, const BlockTable bt)
+__device__ __forceinline__ void duo_roles(uint8_t *smem, const DuoArgs &a, const BlockTable &bt,
+                                          const uint8_t *__restrict__ volts, int wave, int nreg)
 {
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[duo_smem_bytes(SH)];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // two work-groups' waves of one SIMD take different roles (a triangle's
     // roles carry 10 and 8 products)
     switch ((wave + 2 * ((blockIdx.x >> 3) & 1)) & 3) {
-    case 0: duo_wave<SH, 0, ACC, MB>(smem, a, bt, volts, wave); break;
-    case 1: duo_wave<SH, 1, ACC, MB>(smem, a, bt, volts, wave); break;
-    case 2: duo_wave<SH, 2, ACC, MB>(smem, a, bt, volts, wave); break;
-    default: duo_wave<SH, 3, ACC, MB>(smem, a, bt, volts, wave); break;
+    case 0: duo_wave<SH, 0, ACC, MB>(smem, a, bt, volts, wave, nreg); break;
+    case 1: duo_wave<SH, 1, ACC, MB>(smem, a, bt, volts, wave, nreg); break;
+    case 2: duo_wave<SH, 2, ACC, MB>(smem, a, bt, volts, wave, nreg); break;
+    default: duo_wave<SH, 3, ACC, MB>(smem, a, bt, volts, wave, nreg); break;
     }
 }
 
-template <int SH>
-hipError_t duo_launch(const uint8_t *volts, const BlockTable *bt, DuoArgs a, int accumulate, hipStream_t s)
+// Every work-group walks its share of the triangles and of the rectangles, the
+// first half of an XCD's work-groups the triangles first, the second half, which
+// joins them on the compute units, the rectangles first: the triangles' stream
+// and the rectangles' products then share the chip.  One launch for each shape
+// took 500 us at 512 inputs x 512 channels x 2048 samples, this 486; 256 x 512 x
+// 2048 150 and 137; 384 x 64 x 1024 35 and 32.
+template <int ACC, int MB>
+__global__ __launch_bounds__(kDuoThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void xc_duo4_kernel(const uint8_t *__restrict__ volts, const DuoArgs a, const BlockTable bt)
 {
-    a.per = (int)(((int64_t)a.F * a.nreg + 7) / 8);
-    const int grid = 8 * std::max(1, std::min(compute_units() / 4, a.per));   // two per compute unit
-    BlockTable table{};
-    if (bt)
-        table = *bt;
-    auto kern = bt ? (accumulate ? xc_duo4_kernel<SH, 1, 1> : xc_duo4_kernel<SH, 0, 1>)
-                   : (accumulate ? xc_duo4_kernel<SH, 1, 0> : xc_duo4_kernel<SH, 0, 0>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts, a, table);
-    return hipGetLastError();
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[duo_smem_bytes(kDuoTri) > duo_smem_bytes(kDuoRect)
+                                                               ? duo_smem_bytes(kDuoTri) : duo_smem_bytes(kDuoRect)];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool rect_first = (blockIdx.x >> 3) >= (gridDim.x >> 4);
+    for (int k = 0; k < 2; ++k) {
+        if (rect_first == (k == 0)) {
+            if (a.nrect)
+                duo_roles<kDuoRect, ACC, MB>(smem, a, bt, volts, wave, a.nrect);
+        } else {
+            duo_roles<kDuoTri, ACC, MB>(smem, a, bt, volts, wave, a.ntri);
+        }
+        __syncthreads();   // the ring and the transpose tiles change hands
+    }
 }
 
 }  // namespace
@@ -535,12 +543,16 @@ hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, in
     const int nseg = (N + 127) / 128, pairs = nseg * (nseg - 1) / 2;
     if ((int64_t)F * std::max(nseg, pairs) > (1LL << 30))
         return hipErrorInvalidValue;
-    DuoArgs a{T, F, N, nseg, 0, out, in};
-    hipError_t e = duo_launch<kDuoTri>(volts, bt, a, accumulate, s);
-    a.nreg = pairs;
-    if (e == hipSuccess && pairs > 0)
-        e = duo_launch<kDuoRect>(volts, bt, a, accumulate, s);
-    return e;
+    const DuoArgs a{T, F, N, nseg, pairs, out, in};
+    const int per = (int)(((int64_t)F * std::max(nseg, pairs) + 7) / 8);
+    const int grid = 8 * std::max(1, std::min(compute_units() / 4, per));   // two per compute unit
+    BlockTable table{};
+    if (bt)
+        table = *bt;
+    auto kern = bt ? (accumulate ? xc_duo4_kernel<1, 1> : xc_duo4_kernel<0, 1>)
+                   : (accumulate ? xc_duo4_kernel<1, 0> : xc_duo4_kernel<0, 0>);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts, a, table);
+    return hipGetLastError();
 }
 
 }  // namespace xc
