@@ -512,9 +512,10 @@ bool split_words(const void *volts, int F, int N, int bps)
 // 2048 25 and 29, 128 x 1024 26 and 21; 128 inputs: 64 x 4096 20 and 31, 128 x
 // 1024 15 and 12; 256 x 64 x 1024 24 and 30; 384 x 64 x 1024 47 and 34; 512 x 16
 // x 2048 33 and 49; 64 inputs x 8192: 256 channels 29 and 69, 1024 channels 155
-// and 138; 8+8-bit, 192 inputs x 8192: 32 channels 45 and 147 (FP16 68 and 272),
-// 128 channels 149 and 150 (200 and 276); 128 inputs x 512 channels x 8192: 311
-// and 238 (387 and 385).  It is taken only where the estimate is 10 % better.
+// and 138; 8+8-bit, 192 inputs x 8192: 32 channels 51 and 138 (FP16 69 and 200),
+// 128 channels 142 and 142 (215 and 204); 128 inputs x 128 channels x 4096: 48
+// and 47 (63 and 71); FP16 96 x 128 x 4096 61 and 54, 64 x 256 x 8192 57 and 86.
+// It is taken only where the estimate is 10 % better.
 namespace {
 struct SplitCost {
     double one, one_load, two;                   // per sample: one-block regions (base, per load), two-block ones
@@ -526,7 +527,7 @@ struct SplitCost {
 };
 constexpr SplitCost kCost4{0.001, 0.0037, 0.0034, 3.5, 4.5, 7.0, 7.0, 7.0, 0.0078, 0.0088, 0.0117, 0.0117, 0.0117, true, false, true};
 constexpr SplitCost kCost8{0.0015, 0.0062, 0.0052, 2.5, 4.0, 5.0, 9.5, 7.0, 0.0063, 0.0083, 0.0105, 0.0170, 0.0140, false, true, false};
-constexpr SplitCost kCost8H{0.0026, 0.006, 0.0072, 3.0, 4.5, 5.0, 9.5, 8.0, 0.0102, 0.0152, 0.0195, 0.0317, 0.0312, false, true, false};
+constexpr SplitCost kCost8H{0.0026, 0.006, 0.0072, 3.0, 4.5, 5.0, 9.5, 8.0, 0.0088, 0.0120, 0.0160, 0.0245, 0.0215, false, true, false};
 
 int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
 {
