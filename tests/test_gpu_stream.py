@@ -231,3 +231,12 @@ def test_pipe_dump_written_by_the_last_ingest(every, bits):
     assert np.array_equal(tail.cpu().numpy(), want(blocks[2 * every:]))
     p.close()
     c.close()
+
+
+def test_calls_go_to_the_current_stream():
+    side = torch.cuda.Stream()
+    assert X._stream_handle(None) == (torch.cuda.current_stream().cuda_stream or None)
+    with torch.cuda.stream(side):
+        assert X._stream_handle(None) == side.cuda_stream
+    assert X._stream_handle(None) == (torch.cuda.current_stream().cuda_stream or None)
+    assert X._stream_handle(side) == side.cuda_stream and X._stream_handle(0) is None
