@@ -182,7 +182,9 @@ int xcorr_destroy(xcorr_ctx *ctx);
 /*
  * Batched launch (4+4-bit, int8-MFMA contexts only).  The X-engine of
  * Section 2.3 runs once per array; a batch correlates up to XCORR_MAX_BATCH
- * arrays of uneven N, F and sample count in one kernel launch.  Where every
+ * arrays of uneven N, F and sample count in one kernel launch (a member that
+ * fills the chip with a kernel for its size gets a launch of its own ahead of
+ * it, on the same stream).  Where every other
  * array has N a multiple of 16 and a 16-byte-aligned input, each array's
  * region shapes are jobs of the three-product kernel that every work-group
  * walks in turn; otherwise one kernel drains a work queue of (array,

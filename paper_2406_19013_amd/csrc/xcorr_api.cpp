@@ -285,6 +285,22 @@ hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out,
     return xc::launch_mfma4f(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
 }
 
+// Whether a member of a batch is launched by itself: the kernel for its size
+// fills the chip with it and starts an integration.  Measured with the dumps
+// (us, in the shared launch and by themselves): 64 x 256 + 192 x 1024 + 256 x
+// 512 + 512 x 128, 2048 samples 613 and 579; 256 x 512 twice, 64 samples 210 and
+// 198; 512 x 128 + 16 x 8, 2048 samples 195 and 172.  One triangle of 129 to 192
+// inputs gains from about 1024 samples on (192 x 256 twice, 64 samples 48 and
+// 53), and with running sums nothing does (545 and 542 without the dumps).
+bool batch_alone(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, bool accumulate)
+{
+    const int F = ctx->cfg.n_chans, N = ctx->cfg.n_inputs;
+    if (accumulate || !free_choice(ctx) || N % 16 || (uintptr_t)v % 16 || !word_rows(ctx->cfg, v) ||
+        !xc::gauss4_runs(ctx->plan, F, N))
+        return false;
+    return (xc::duo4_taken(N, T) && (int64_t)F * ((N + 127) / 128) >= 512) || (xc::tri48_taken(N) && F >= 256 && T >= 1024);
+}
+
 // One MFMA-path launch of either sample format (not the per-role kernel):
 // results to `out`, running sums (accumulate = 1) from acc_in.
 hipError_t launch_mfma(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, void *out, int accumulate, hipStream_t s,
@@ -694,12 +710,18 @@ int xcorr_batch_ingest(xcorr_batch *b, const void *const *d_volts, const int64_t
         xc::BatchArgs args{};
         int vec = 1;
         int64_t items = 0;
+        int alone[xc::kMaxBatchArrays], n_alone = 0;
         for (int a = 0; a < n; ++a) {
             if (n_samples[a] <= t0)
                 continue;
             const xcorr_ctx *c = b->ctx[a];
             const xc::Plan &pl = b->plan[a];
             const int F = c->cfg.n_chans, N = c->cfg.n_inputs;
+            if (batch_alone(c, static_cast<const uint8_t *>(d_volts[a]) + t0 * (int64_t)F * N,
+                            std::min(L, n_samples[a] - t0), c->acc_samples > 0 || t0 > 0)) {
+                alone[n_alone++] = a;
+                continue;
+            }
             xc::BatchArray &A = args.a[args.n++];
             A.volts = static_cast<const uint8_t *>(d_volts[a]) + t0 * (int64_t)F * N;
             A.acc = static_cast<int2 *>(c->ws);
@@ -723,8 +745,16 @@ int xcorr_batch_ingest(xcorr_batch *b, const void *const *d_volts, const int64_t
         bool gauss = kernel4_from_env() == Kernel4::Gauss;
         for (int a = 0; a < args.n && gauss; ++a)
             gauss = xc::gauss4_batch_supported(args.a[a]);
-        const hipError_t e = gauss ? xc::launch_gauss4_batch(args, b->grid, s)
-                                   : xc::launch_batch4(args, b->queue, vec, std::min<int64_t>(b->grid, items), s);
+        hipError_t e = hipSuccess;
+        for (int k = 0; k < n_alone && e == hipSuccess; ++k) {
+            const xcorr_ctx *c = b->ctx[alone[k]];
+            const int64_t row = (int64_t)c->cfg.n_chans * c->cfg.n_inputs;
+            e = launch4(c, static_cast<const uint8_t *>(d_volts[alone[k]]) + t0 * row,
+                        std::min(L, n_samples[alone[k]] - t0), static_cast<int2 *>(c->ws), 0, s);
+        }
+        if (e == hipSuccess && args.n > 0)
+            e = gauss ? xc::launch_gauss4_batch(args, b->grid, s)
+                      : xc::launch_batch4(args, b->queue, vec, std::min<int64_t>(b->grid, items), s);
         if (e != hipSuccess)
             return hip_fail(e, "batch launch");
         for (int a = 0; a < n; ++a)

@@ -649,7 +649,7 @@ class Correlator:
 class Batch:
     """A batched persistent launch over several Correlators (4+4-bit int8 MFMA).
 
-    ``ingest([volts_0, volts_1, ...])`` correlates every array in one kernel;
+    ``ingest([volts_0, volts_1, ...])`` correlates every array with one call;
     dumps stay per Correlator.  The Correlators must outlive the Batch.
     """
 

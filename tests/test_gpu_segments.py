@@ -97,3 +97,22 @@ def test_oracle_parity():
         v = synth.uniform_volts4(N, F, T, seed=(2304, N))
         want = oracle.to_int32(oracle.xcorr(v.numpy(), 4, T, F, N))
         assert np.array_equal(_run(v.cuda(), N, F, [T]).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("T", [64, 1100])
+def test_batch_members_launched_by_themselves(T):
+    """Members that fill the chip beside ones that share a launch, and alone;
+    the second ingest adds to running sums."""
+    arrays = [(256, 264), (64, 8), (192, 256), (512, 128)]
+    for pick in (arrays, arrays[:1]):
+        vs = [synth.uniform_volts4(N, F, T, seed=(2305, T, N), device="cuda") for N, F in pick]
+        cors = [X.Correlator(N, F) for N, F in pick]
+        b = X.Batch(cors)
+        for _ in range(2):
+            b.ingest(vs)
+        for (N, F), v, c in zip(pick, vs, cors):
+            out, n, _ = c.dump()
+            torch.cuda.synchronize()
+            assert n == 2 * T and c.stats()["kernel_launches"] == 3
+            assert torch.equal(out, 2 * _run(v, N, F, [T], X.PATH_PLAIN)), (N, F)
+        b.close()
