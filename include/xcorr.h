@@ -184,12 +184,11 @@ int xcorr_destroy(xcorr_ctx *ctx);
  * Section 2.3 runs once per array; a batch correlates up to XCORR_MAX_BATCH
  * arrays of uneven N, F and sample count in one kernel launch (a member that
  * fills the chip with a kernel for its size gets a launch of its own ahead of
- * it, on the same stream).  Where every other
- * array has N a multiple of 16 and a 16-byte-aligned input, each array's
- * region shapes are jobs of the three-product kernel that every work-group
- * walks in turn; otherwise one kernel drains a work queue of (array,
- * channel, region) items.  Results, the integration bookkeeping and the
- * dumps stay per context (xcorr_dump).
+ * it, on the same stream).  Where every array of that launch has N a multiple
+ * of 16 and a 16-byte-aligned input, each array's region shapes are jobs of the
+ * three-product kernel that every work-group walks in turn; otherwise one
+ * kernel drains a work queue of (array, channel, region) items.  Results, the
+ * integration bookkeeping and the dumps stay per context (xcorr_dump).
  *
  * xcorr_batch_query: device bytes the batch needs (the work-queue counters).
  * xcorr_batch_init : ctxs[0..n) are borrowed (they must outlive the batch and
