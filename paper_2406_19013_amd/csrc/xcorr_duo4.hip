@@ -24,7 +24,7 @@
 // samples, 1.2 GB: 292 -> 260 us, 4.7 TB/s); for rectangles the power that the
 // products draw, then each segment's samples being read once per pair of
 // segments.  Against the three-product kernel: 512 inputs x 512 channels x 2048
-// samples 570 -> 486 us; 256 x 512 x 2048 162 -> 137; 200 x 512 x 2000 152 ->
+// samples 570 -> 481 us; 256 x 512 x 2048 162 -> 136; 200 x 512 x 2000 152 ->
 // 125; 1024 x 64 x 2048 267 -> 228; 128 x 256 x 4096 60 -> 37 (that kernel
 // takes channels in pairs, which leaves half the chip idle).
 #include "xc_mfma4.h"
@@ -41,11 +41,13 @@ constexpr int duo_blocks(int SH) { return SH == kDuoTri ? 4 : 8; }
 constexpr int duo_rows(int SH) { return SH == kDuoRect ? 64 : 128; }   // time rows per ring slot
 constexpr int duo_row_bytes(int SH) { return 32 * duo_blocks(SH); }
 constexpr int duo_slot_bytes(int SH) { return duo_rows(SH) * duo_row_bytes(SH); }
-constexpr int duo_nbuf(int SH) { return SH == kDuoTri ? 3 : 4; }
+// ring slots of 16 KB (a fourth for rectangles: 139 us for 136 at 256 inputs x
+// 512 channels x 2048 samples, nothing elsewhere)
+constexpr int kDuoNbuf = 3;
 constexpr int kDuoTrStride = 33;                    // ints per row of a transpose tile
 constexpr int duo_smem_bytes(int SH)
 {
-    return duo_nbuf(SH) * duo_slot_bytes(SH) + (SH == kDuoRect ? 0 : 2 * 32 * kDuoTrStride * 4);
+    return kDuoNbuf * duo_slot_bytes(SH) + (SH == kDuoRect ? 0 : 2 * 32 * kDuoTrStride * 4);
 }
 // 16-byte unit u of time row r lies at u ^ duo_swizzle: the 8 rows x 2 units of
 // a transpose read by 32 lanes fall on 64 distinct banks
@@ -148,7 +150,7 @@ template <int SH, int ROLE, int ACC, int MB>
 __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const BlockTable &bt,
                                          const uint8_t *__restrict__ volts, int wave, int nreg)
 {
-    constexpr int NB = duo_blocks(SH), ROW = duo_row_bytes(SH), SLOT = duo_slot_bytes(SH), NBUF = duo_nbuf(SH);
+    constexpr int NB = duo_blocks(SH), ROW = duo_row_bytes(SH), SLOT = duo_slot_bytes(SH), NBUF = kDuoNbuf;
     constexpr int C = duo_rows(SH), STEPS = C / 32;
     constexpr int U = 2 * NB;                             // 16-byte units per row
     constexpr int LOADS = SLOT / 1024 / kDuoWaves;            // loads per wave and chunk
