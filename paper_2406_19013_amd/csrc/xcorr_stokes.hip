@@ -16,17 +16,22 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 namespace xc {
 namespace {
 
 constexpr int kStokesChans = 4;   // channels per thread (the pair's indices are formed once)
+// A launch counts the threads of each grid dimension in 32 bits and drops the
+// rest without an error: a row of the grid is at most this many work-groups,
+// and further ones go along z.
+constexpr int64_t kStokesRow = 1 << 22;
 
 __global__ __launch_bounds__(256) void xc_stokes_kernel(const int2 *__restrict__ vis, int F, int64_t P, int64_t Pf,
                                                         longlong2 *__restrict__ out)
 {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;   // (feed pair, parameter)
+    const int64_t e = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * 256 + threadIdx.x;   // (feed pair, parameter)
     const int64_t q = e >> 2;
     const int s = (int)(e & 3);
     if (q >= Pf)
@@ -68,10 +73,11 @@ extern "C" int xcorr_stokes(const void *d_vis, int32_t n_inputs, int32_t n_chans
         return XCORR_E_INVAL;
     const int nf = n_inputs / 2;
     const int64_t P = (int64_t)n_inputs * (n_inputs + 1) / 2, Pf = (int64_t)nf * (nf + 1) / 2;
-    if ((4 * Pf + 255) / 256 > 0x7fffffff)
+    const int64_t blocks = (4 * Pf + 255) / 256, row = std::min(blocks, kStokesRow), rows = (blocks + row - 1) / row;
+    if (rows > 65535)
         return XCORR_E_INVAL;
-    hipLaunchKernelGGL(xc_stokes_kernel, dim3((unsigned)((4 * Pf + 255) / 256),
-                       (unsigned)((n_chans + kStokesChans - 1) / kStokesChans)), dim3(256), 0,
+    hipLaunchKernelGGL(xc_stokes_kernel,
+                       dim3((unsigned)row, (unsigned)((n_chans + kStokesChans - 1) / kStokesChans), (unsigned)rows), dim3(256), 0,
                        reinterpret_cast<hipStream_t>(stream), (const int2 *)d_vis, n_chans, P, Pf, (longlong2 *)d_out);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? XCORR_OK : api_error(XCORR_E_HIP, std::string("stokes launch: ") + hipGetErrorString(e));
