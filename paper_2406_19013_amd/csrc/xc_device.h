@@ -24,11 +24,19 @@ constexpr int kThreads = 256;
 // multiple of 8; callers drop items >= the real count.
 __device__ __forceinline__ int xcd_item()
 {
-    const int per = gridDim.x >> 3;
-    return (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    const int per = (gridDim.x >> 3) * gridDim.y;
+    return (blockIdx.x & 7) * per + (int)blockIdx.y * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
-inline int xcd_grid(int nitems) { return ((nitems + 7) / 8) * 8; }
+// A launch counts the threads of each grid dimension in 32 bits and drops the
+// rest without an error: a row of the grid is at most this many work-groups
+// (of up to 512 threads), and further ones go along y.
+constexpr int kGridRow = 1 << 22;
+inline dim3 xcd_grid(int nitems)
+{
+    const int groups = (nitems + 7) / 8 * 8, rows = (groups + kGridRow - 1) / kGridRow;
+    return dim3(rows > 1 ? kGridRow : groups, rows);
+}
 
 // 16 consecutive bytes of one (t, f) row starting at input i0; zero outside
 // [0,T) x [0,N).  bps = bytes per sample.  vec_ok: rows are 16-byte aligned

@@ -168,10 +168,9 @@ hipError_t launch_plain(int bits, const uint8_t *volts, int64_t T, int F, int N,
     const int nitems = (int)nitems64;
     const int bps = bits == 4 ? 1 : 2;
     const int vec_ok = ((int64_t)N * bps % 16 == 0) && ((uintptr_t)volts % 16 == 0);
-    dim3 grid(xcd_grid(nitems)), block(kThreads);
     auto kern = bits == 4 ? (vec_ok ? xc_plain_kernel<4, 1> : xc_plain_kernel<4, 0>)
                           : (vec_ok ? xc_plain_kernel<8, 1> : xc_plain_kernel<8, 0>);
-    hipLaunchKernelGGL(kern, grid, block, 0, s, volts, T, F, N, ntiles, nitems, acc, accumulate);
+    hipLaunchKernelGGL(kern, xcd_grid(nitems), dim3(kThreads), 0, s, volts, T, F, N, ntiles, nitems, acc, accumulate);
     return hipGetLastError();
 }
 

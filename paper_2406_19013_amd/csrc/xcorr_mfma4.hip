@@ -54,7 +54,7 @@ static hipError_t launch_mfma4_t(const Plan &pl, const uint8_t *volts, int64_t T
     const int vec_ok = (N % 16 == 0) && ((uintptr_t)volts % 16 == 0) &&
                        (int64_t)KC * F * N < (1LL << 31) - 16;
     auto kern = vec_ok ? xc_mfma4_kernel<D, KC, 1> : xc_mfma4_kernel<D, KC, 0>;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(nitems)), dim3(kMfmaThreads), 0, s, volts, T, F, N,
+    hipLaunchKernelGGL(kern, xcd_grid(nitems), dim3(kMfmaThreads), 0, s, volts, T, F, N,
                        pl.nseg, pl.regions, nitems, acc, accumulate);
     return hipGetLastError();
 }

@@ -87,7 +87,7 @@ static hipError_t launch_mfma4f_blocks_t(const Plan &pl, const BlockTable &bt, i
     const int nitems = (int)nitems64;
     const int64_t T = (int64_t)n_blocks * bt.chunks_per_block * 64;
     auto kern = accumulate ? xc_mfma4f_blocks_kernel<D, 1> : xc_mfma4f_blocks_kernel<D, 0>;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(nitems)), dim3(kMfmaThreads), 0, s, bt, T, F, N, pl.nseg, pl.regions,
+    hipLaunchKernelGGL(kern, xcd_grid(nitems), dim3(kMfmaThreads), 0, s, bt, T, F, N, pl.nseg, pl.regions,
                        nitems, acc, acc_in ? acc_in : acc, accumulate);
     return hipGetLastError();
 }
@@ -127,7 +127,7 @@ static hipError_t launch_mfma4f_t(const Plan &pl, const uint8_t *volts, int64_t 
     // accumulating epilogue cost the overwriting one registers and time
     auto kern = vec_ok ? (accumulate ? xc_mfma4f_kernel<D, 1, 1> : xc_mfma4f_kernel<D, 1, 0>)
                        : (accumulate ? xc_mfma4f_kernel<D, 0, 1> : xc_mfma4f_kernel<D, 0, 0>);
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(nitems)), dim3(kMfmaThreads), 0, s, volts, T, F, N,
+    hipLaunchKernelGGL(kern, xcd_grid(nitems), dim3(kMfmaThreads), 0, s, volts, T, F, N,
                        pl.nseg, pl.regions, nitems, acc, acc_in ? acc_in : acc, accumulate);
     return hipGetLastError();
 }

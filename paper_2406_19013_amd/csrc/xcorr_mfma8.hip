@@ -552,7 +552,7 @@ static hipError_t launch_mfma8_t(const Plan &pl, const uint8_t *volts, int64_t T
     const int vec_ok = (N % 2 == 0) && ((uintptr_t)volts % 4 == 0) &&
                        (int64_t)KC * F * N * 2 < (1LL << 31) - 16;
     auto kern = vec_ok ? xc_mfma8_kernel<D, F16, KC, 1> : xc_mfma8_kernel<D, F16, KC, 0>;
-    hipLaunchKernelGGL(kern, dim3(xcd_grid(nitems)), dim3(kMfmaThreads), 0, s, volts, T, F, N, pl.nseg,
+    hipLaunchKernelGGL(kern, xcd_grid(nitems), dim3(kMfmaThreads), 0, s, volts, T, F, N, pl.nseg,
                        pl.regions, nitems, acc, acc_in, accumulate);
     return hipGetLastError();
 }

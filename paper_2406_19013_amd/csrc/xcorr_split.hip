@@ -490,7 +490,7 @@ hipError_t split_launch(const uint8_t *volts, const BlockTable *bt, int64_t T, i
             table = *bt;
             kern = accumulate ? xc_split_kernel<FMT, RB, 1, 1, 1> : xc_split_kernel<FMT, RB, 1, 0, 1>;
         }
-    hipLaunchKernelGGL(kern, dim3(xcd_grid((int)items)), dim3(kSpThreads), 0, s, volts, a, table);
+    hipLaunchKernelGGL(kern, xcd_grid((int)items), dim3(kSpThreads), 0, s, volts, a, table);
     return hipGetLastError();
 }
 
