@@ -188,8 +188,9 @@ def bench_precision8(dev, stream, reps: int) -> dict:
 
 def bench_batched(dev, stream, reps: int) -> dict:
     """Four arrays (64x256, 192x1024, 256x512, 512x128 inputs x channels,
-    2048 samples) in one launch, the same launch replayed from a HIP graph,
-    and one launch per array and region shape."""
+    2048 samples) in one batched call, with the library's choice of launches
+    and with tuned tiles (one shared launch); the first replayed from a HIP
+    graph; and one call per array."""
     import torch
 
     from paper_2406_19013_amd import synth
@@ -199,19 +200,29 @@ def bench_batched(dev, stream, reps: int) -> dict:
         vs = synth.batched(device=dev)
     stream.synchronize()
     T = vs[0].shape[0]
-    # tiles tuned on the batched kernel into a private tune cache
+    # the library's choice of launches, and one shared launch of every array
+    # with tiles tuned on the batched kernel into a private tune cache
     import tempfile
     cache_dir = tempfile.mkdtemp(prefix="xcorr_tune_")
-    prev_cache = os.environ.get("XCORR_TUNE_CACHE")
-    os.environ["XCORR_TUNE_CACHE"] = os.path.join(cache_dir, "tune.txt")
-    tuned = [X.autotune(N, F, device=dev, stream=stream, batch=True) for N, F in synth.BATCH_ARRAYS]
+    prev_cache = os.environ.pop("XCORR_TUNE_CACHE", None)
     cors = [X.Correlator(N, F, 4, X.PATH_I8_MFMA, device=dev) for N, F in synth.BATCH_ARRAYS]
     cmac = sum(N * (N + 1) // 2 * F * T for N, F in synth.BATCH_ARRAYS)
     b = X.Batch(cors, device=dev)
     outs = [torch.empty((F, N * (N + 1) // 2, 2), dtype=torch.int32, device=dev) for N, F in synth.BATCH_ARRAYS]
+    os.environ["XCORR_TUNE_CACHE"] = os.path.join(cache_dir, "tune.txt")
+    tuned = [X.autotune(N, F, device=dev, stream=stream, batch=True) for N, F in synth.BATCH_ARRAYS]
+    tuned_cors = [X.Correlator(N, F, 4, X.PATH_I8_MFMA, device=dev) for N, F in synth.BATCH_ARRAYS]
+    tb = X.Batch(tuned_cors, device=dev)
+    os.environ.pop("XCORR_TUNE_CACHE")
+    if prev_cache is not None:
+        os.environ["XCORR_TUNE_CACHE"] = prev_cache
 
     def dumps():
         for c, o in zip(cors, outs):
+            c.dump(o, stream=stream)
+
+    def tuned_dumps():
+        for c, o in zip(tuned_cors, outs):
             c.dump(o, stream=stream)
 
     def singles():
@@ -229,29 +240,28 @@ def bench_batched(dev, stream, reps: int) -> dict:
         with torch.cuda.stream(stream):
             g.replay()
 
-    # the three ways take turns over several rounds (the part's clock drifts
+    # the four ways take turns over several rounds (the part's clock drifts
     # as it warms, which would favour whichever ran first); medians per launch
     import numpy as np
-    ways = {"batch": lambda: b.ingest(vs, stream=stream), "separate": singles, "graph": replay}
+    ways = {"batch": lambda: b.ingest(vs, stream=stream), "tuned": lambda: tb.ingest(vs, stream=stream),
+            "separate": singles, "graph": replay}
     samples = {k: [] for k in ways}
     rounds = 5
     for _ in range(rounds):
         for k, fn in ways.items():
-            _, ms = _timed(fn, stream, max(2, reps // rounds), after=dumps)
+            _, ms = _timed(fn, stream, max(2, reps // rounds), after=tuned_dumps if k == "tuned" else dumps)
             samples[k].extend(ms.tolist())
     stream.synchronize()
-    batch_ms, single_ms, graph_ms = (float(np.median(samples[k])) for k in ("batch", "separate", "graph"))
-    if prev_cache is None:
-        os.environ.pop("XCORR_TUNE_CACHE", None)
-    else:
-        os.environ["XCORR_TUNE_CACHE"] = prev_cache
+    batch_ms, tuned_ms, single_ms, graph_ms = (float(np.median(samples[k])) for k in ways)
     res = {"workload": "batched-4arrays-2048t-4bit", "arrays": [list(a) for a in synth.BATCH_ARRAYS],
-           "tiles": b.tiles, "tuned_tiles": tuned, "batch_ms": batch_ms, "graph_replay_ms": graph_ms,
+           "tiles": b.tiles, "tuned_tiles": tuned, "batch_ms": batch_ms, "tuned_one_launch_ms": tuned_ms,
+           "graph_replay_ms": graph_ms,
            "separate_launches_ms": single_ms,
            "cmac_per_s": cmac / (batch_ms / 1e3), "frac_of_int8_peak": OPS_PER_CMAC * cmac / (batch_ms / 1e3) / 1e12
            / INT8_PEAK_TOPS}
     b.close()
-    for c in cors:
+    tb.close()
+    for c in cors + tuned_cors:
         c.close()
     return res
 
@@ -641,9 +651,7 @@ def main():
     achieved_tops = algo_ops / ingest_s / 1e12
     in_bytes = T * F * N
     acc_bytes = F * P * 8
-    # the kernel of one 192-input launch: the library's choice, or the tuner's
-    # name for a named tile
-    kernel = X.xcorr_autotune_kernel(mf.cfg) if args.tile else "xc_tri48_kernel"
+    kernel = X.xcorr_ingest_kernel(mf.cfg, volts, T)
     traffic = measured_traffic(kernel)
     dump_gbs = 2 * acc_bytes / (float(dump_ms.mean()) / 1e3) / 1e9
 

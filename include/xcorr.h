@@ -78,7 +78,8 @@ typedef struct {
     int32_t tile;         /* MFMA paths: diagonal block size D in 32-input
                              blocks: 2..4 for any N (1 only when N <= 32),
                              5 or 6 only when N <= 32*D; 0 = tuned value from
-                             the tune cache, else a built-in choice */
+                             the tune cache, else the library chooses the
+                             kernel of each launch by its size */
     int64_t max_samples_per_dump; /* 0 = the format's T_max; larger than
                                      T_max is XCORR_E_OVERFLOW */
 } xcorr_config;
@@ -91,8 +92,10 @@ typedef struct {
     int64_t kernel_launches;
     uint64_t seq_gaps;          /* missing sequence numbers since the last dump */
     uint64_t seq_gaps_total;
-    int32_t tile;               /* diagonal block size in use (MFMA paths) */
-    int32_t regions_per_chan;   /* work-groups per channel in one ingest */
+    int32_t tile;               /* diagonal block size of the plan (MFMA paths): the tile of the
+                                   config or the tune cache, else the built-in one, which only
+                                   kernels that take a tile follow (xcorr_ingest_kernel) */
+    int32_t regions_per_chan;   /* regions per channel of that plan */
     int32_t tile_from_cache;    /* 1: the tile came from a tune-cache line */
 } xcorr_stats_t;
 
@@ -184,7 +187,7 @@ int xcorr_destroy(xcorr_ctx *ctx);
  * Section 2.3 runs once per array; a batch correlates up to XCORR_MAX_BATCH
  * arrays of uneven N, F and sample count in one kernel launch (a member that
  * fills the chip with a kernel for its size gets a launch of its own ahead of
- * it, on the same stream).  Where every array of that launch has N a multiple
+ * it, on the same stream, unless its tile is named by its config or tuned).  Where every array of that launch has N a multiple
  * of 16 and a 16-byte-aligned input, each array's region shapes are jobs of the
  * three-product kernel that every work-group walks in turn; otherwise one
  * kernel drains a work queue of (array, channel, region) items.  Results, the
@@ -197,7 +200,7 @@ int xcorr_destroy(xcorr_ctx *ctx);
  *   with a synchronous kernel on the null stream.  Each array keeps its own
  *   region plan when its tile is 2, 3, 4, or 6 with N <= 192; other tiles are
  *   replaced by whichever of 2, 3, 4 pads least (xcorr_batch_tiles reports
- *   the choice).
+ *   the plans of the shared launch).
  *   Errors: XCORR_E_INVAL (n outside 1..XCORR_MAX_BATCH, a NULL or repeated
  *   context, a context that is not 4-bit int8-MFMA), XCORR_E_NOMEM, XCORR_E_HIP.
  * xcorr_batch_ingest: d_volts[a] = [n_samples[a]][F_a][N_a] for array a;
@@ -223,16 +226,21 @@ int xcorr_batch_destroy(xcorr_batch *b);
 /*
  * Autotuner (the triangle-tile choice of the work split; the paper's X-engine
  * runs a fixed tiling, Section 2.3).  xcorr_autotune times every supported
- * tile of an MFMA-path config on the kernel a context of that config runs
+ * tile of an MFMA-path config on the kernel that runs where that tile is named
  * (xcorr_autotune_kernel names it), over a synthetic block of 2048 samples
  * (a fixed hash pattern written into the scratch), and returns the fastest
  * in *best_tile.  xcorr_autotune_batch does the same on the batched
  * persistent kernel, with the config as its only array, over the tiles that
  * kernel carries (2, 3, 4, and 6 when N <= 192).  When $XCORR_TUNE_CACHE
  * names a file, the line "bits N F path tile kernel" is appended to it;
- * xcorr_init with tile = 0 (and xcorr_batch_init, for each member) then uses
- * the last line of that config whose kernel is the one it will run; lines
- * timed on another kernel are ignored.  xcorr_plan_tile (pure host) reports
+ * xcorr_init with tile = 0 (and xcorr_batch_init, for each member) then takes
+ * the last line of that config whose kernel is the one that tile runs, as if
+ * the config named the tile; lines timed on another kernel are ignored.  With
+ * neither a tile nor a line the library chooses the kernel of each launch by
+ * its size, also among kernels that take no tile and are often faster than
+ * every tile: xcorr_ingest_kernel (pure host) names the one that the first
+ * launch of xcorr_ingest(d_volts, n_samples) runs in a context of this config
+ * (d_volts counts by its alignment only).  xcorr_plan_tile (pure host) reports
  * the tile xcorr_init (batch = 0) or xcorr_batch_init (batch = 1) would use
  * and whether it came from the cache.  The tuners block until their timing
  * runs on `stream` have finished.  xcorr_autotune_query gives the scratch
@@ -247,6 +255,7 @@ int xcorr_autotune(const xcorr_config *cfg, void *d_scratch, size_t scratch_byte
 int xcorr_autotune_batch(const xcorr_config *cfg, void *d_scratch, size_t scratch_bytes, void *stream,
                          int32_t *best_tile);
 int xcorr_autotune_kernel(const xcorr_config *cfg, int32_t batch, char *name, size_t len);
+int xcorr_ingest_kernel(const xcorr_config *cfg, const void *d_volts, int64_t n_samples, char *name, size_t len);
 int xcorr_plan_tile(const xcorr_config *cfg, int32_t batch, int32_t *tile, int32_t *from_cache);
 /*
  * Streaming loop (the X-engine node's packet ring feeding the correlator,

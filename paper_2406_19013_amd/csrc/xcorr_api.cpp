@@ -27,6 +27,7 @@ struct xcorr_ctx {
     int kc;
     Kernel4 k4;
     int tile_from_cache;   // the tile came from a tune-cache line
+    bool tile_named;       // the config or the cache names the tile: its kernels run
     void *ws;
     size_t ws_bytes;
     int64_t t_max;
@@ -101,27 +102,74 @@ bool gauss_runs(Kernel4 k, const xc::Plan &pl, int F, int N)
     return k == Kernel4::Gauss && xc::gauss4_supported(pl, F, N);
 }
 
-int default_tile(int N);
+// Rows of this array that start on 4-byte boundaries, which LDS-DMA needs
+// (and offsets within a 64-sample chunk that fit its 32 bits).
+bool word_rows(const xcorr_config &c, const void *v)
+{
+    return c.n_inputs % 4 == 0 && (uintptr_t)v % 4 == 0 && 64LL * c.n_chans * c.n_inputs < (1LL << 31) - 16;
+}
 
-// Name of the kernel an ingest of this config with this tile launches
-// (batch = 0) or that the batched launch runs for it (batch = 1); the tuner
-// times that kernel and labels its tune-cache line with this name.
+// The kernel of one MFMA-path launch.
+enum class Launch { Roles4, Fused4, Gauss4, Split4, Duo4, Tri48, Mfma8, Split8 };
+struct Choice {
+    Launch kernel;
+    int rb = 0;   // Split4, Split8: blocks along a region's side
+};
+
+// The kernel that correlates T samples at v (one launch's worth, or a table of
+// 16-byte-aligned blocks that starts with v).  named: the tile was named, by
+// the config or by a tune-cache line, and the kernels that take tiles run with
+// that plan, as the tuner timed them; otherwise (or with the environment naming
+// another 4+4-bit family) the library chooses by size and alignment.
+Choice choose(const xcorr_config &c, const xc::Plan &pl, Kernel4 k4, bool named, const void *v, int64_t T)
+{
+    const int F = c.n_chans, N = c.n_inputs;
+    if (c.sample_bits == 8) {
+        const int rb = named ? 0 : xc::split8_blocks(pl, c.path == XCORR_PATH_F16_MFMA, static_cast<const uint8_t *>(v), F, N, T);
+        return rb ? Choice{Launch::Split8, rb} : Choice{Launch::Mfma8};
+    }
+    if (k4 == Kernel4::Roles)
+        return {Launch::Roles4};
+    if (k4 == Kernel4::Gauss && !named) {
+        if (word_rows(c, v)) {
+            if (xc::gauss4_runs(pl, F, N)) {
+                if (const int rb = xc::split4_blocks(pl, F, N, T))
+                    return {Launch::Split4, rb};
+                return {xc::duo4_taken(N, T) ? Launch::Duo4 : xc::tri48_taken(N) ? Launch::Tri48 : Launch::Gauss4};
+            }
+        } else if (xc::split4_unaligned(F, N, T)) {
+            return {Launch::Split4, 1};
+        }
+    }
+    return {gauss_runs(k4, pl, F, N) && (uintptr_t)v % 16 == 0 ? Launch::Gauss4 : Launch::Fused4};
+}
+
+const char *launch_name(const xcorr_config &c, Launch k)
+{
+    switch (k) {
+    case Launch::Roles4: return "xc_mfma4_kernel";
+    case Launch::Fused4: return "xc_mfma4f_kernel";
+    case Launch::Gauss4: return "xc_gauss4_kernel";
+    case Launch::Duo4: return "xc_duo4_kernel";
+    case Launch::Tri48: return "xc_tri48_kernel";
+    case Launch::Mfma8: return c.path == XCORR_PATH_F16_MFMA ? "xc_mfma8_kernel_f16" : "xc_mfma8_kernel_i8";
+    default: return "xc_split_kernel";
+    }
+}
+
+// Name of the kernel that runs for this config with this tile named (batch =
+// 0, 16-byte-aligned input), or that the batched launch runs for it (batch =
+// 1): the kernel the tuner times and labels its tune-cache line with.
 const char *kernel_for(const xcorr_config &c, int tile, bool batch)
 {
     if (c.path == XCORR_PATH_PLAIN)
         return "xc_plain_kernel";
+    const xc::Plan pl = xc::make_plan(c.n_inputs, tile);
     if (batch)
-        return kernel4_from_env() == Kernel4::Gauss &&
-                       xc::gauss4_batch_shape(xc::make_plan(c.n_inputs, tile), c.n_chans, c.n_inputs)
+        return kernel4_from_env() == Kernel4::Gauss && xc::gauss4_batch_shape(pl, c.n_chans, c.n_inputs)
                    ? "xc_gauss4_batch_kernel"
                    : "xc_batch4_kernel";
-    if (c.sample_bits == 8)
-        return c.path == XCORR_PATH_F16_MFMA ? "xc_mfma8_kernel_f16" : "xc_mfma8_kernel_i8";
-    const Kernel4 k = kernel4_from_env();
-    if (k == Kernel4::Roles)
-        return "xc_mfma4_kernel";
-    return gauss_runs(k, xc::make_plan(c.n_inputs, tile), c.n_chans, c.n_inputs) ? "xc_gauss4_kernel"
-                                                                                : "xc_mfma4f_kernel";
+    return launch_name(c, choose(c, pl, kernel4_from_env(), true, nullptr, 1).kernel);
 }
 
 // Tiles the batched kernel carries for an array of N inputs.
@@ -210,10 +258,11 @@ int batch_fallback_tile(int N, int own)
 }
 
 // Region plan of a batch member: the tile tuned for the batched kernel
-// (tune cache), else the fallback above.
-xc::Plan batch_plan(const xcorr_ctx *c)
+// (tune cache; *tuned = true), else the fallback above.
+xc::Plan batch_plan(const xcorr_ctx *c, bool *tuned)
 {
     int d = cached_tile(c->cfg, true);
+    *tuned = d != 0;
     if (!d)
         d = batch_fallback_tile(c->cfg.n_inputs, c->plan.D);
     return xc::make_plan(c->cfg.n_inputs, d);
@@ -246,43 +295,36 @@ void note_ingest(xcorr_ctx *ctx, int64_t n_samples, uint64_t seq)
     ++ctx->ingests;
 }
 
-// The library chooses the kernel of a 4+4-bit launch unless the config names
-// a tile (whose kernels then run) or the environment another family.
-bool free_choice(const xcorr_ctx *ctx) { return ctx->k4 == Kernel4::Gauss && ctx->cfg.tile == 0; }
-
-// Rows of this array that start on 4-byte boundaries, which LDS-DMA needs
-// (and offsets within a 64-sample chunk that fit its 32 bits).
-bool word_rows(const xcorr_config &c, const void *v)
-{
-    return c.n_inputs % 4 == 0 && (uintptr_t)v % 4 == 0 && 64LL * c.n_chans * c.n_inputs < (1LL << 31) - 16;
-}
-
-// One 4+4-bit int8-MFMA launch of the kernel family the context runs:
-// results to `out`, running sums (accumulate = 1) from acc_in (default out).
-hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out, int accumulate, hipStream_t s,
-                   const int2 *acc_in = nullptr)
+// One MFMA-path launch: results to `out`, running sums (accumulate = 1) from
+// acc_in (the per-role kernel has them in `out` itself).  bt: the samples are a
+// table of n_blocks blocks, the first at v.
+hipError_t launch_mfma(const xcorr_ctx *ctx, const void *input, const xc::BlockTable *bt, int n_blocks, int64_t T, void *out,
+                       int accumulate, hipStream_t s, const void *acc_in)
 {
     const xcorr_config &c = ctx->cfg;
+    const xc::Plan &pl = ctx->plan;
     const int F = c.n_chans, N = c.n_inputs;
-    if (free_choice(ctx)) {
-        if (word_rows(c, v)) {
-            if (xc::gauss4_runs(ctx->plan, F, N)) {
-                const int2 *in = acc_in ? acc_in : out;
-                if (const int rb = xc::split4_blocks(ctx->plan, F, N, T))
-                    return xc::launch_split4(rb, v, T, F, N, out, accumulate, s, in);
-                if (xc::duo4_taken(N, T))
-                    return xc::launch_duo4(v, nullptr, T, F, N, out, in, accumulate, s);
-                if (xc::tri48_taken(N))
-                    return xc::launch_tri48(v, nullptr, T, F, N, out, in, accumulate, s);
-                return xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, in);
-            }
-        } else if (xc::split4_unaligned(F, N, T)) {
-            return xc::launch_split4(1, v, T, F, N, out, accumulate, s, acc_in);
-        }
+    const bool f16 = c.path == XCORR_PATH_F16_MFMA;
+    const uint8_t *v = static_cast<const uint8_t *>(input);
+    const Choice k = choose(c, pl, ctx->k4, ctx->tile_named, v, T);
+    int2 *const o = static_cast<int2 *>(out);
+    const int2 *const in = static_cast<const int2 *>(acc_in);
+    switch (k.kernel) {
+    case Launch::Split8: return xc::launch_split8(k.rb, f16, v, T, F, N, out, acc_in, accumulate, s);
+    case Launch::Mfma8: return xc::launch_mfma8(pl, f16, v, T, F, N, out, acc_in, accumulate, s);
+    case Launch::Roles4: return xc::launch_mfma4(pl, ctx->kc, v, T, F, N, o, accumulate, s);
+    case Launch::Duo4: return xc::launch_duo4(v, bt, T, F, N, o, in, accumulate, s);
+    case Launch::Tri48: return xc::launch_tri48(v, bt, T, F, N, o, in, accumulate, s);
+    case Launch::Split4:
+        return bt ? xc::launch_split4_blocks(k.rb, *bt, n_blocks, F, N, o, accumulate, s)
+                  : xc::launch_split4(k.rb, v, T, F, N, o, accumulate, s, in);
+    case Launch::Gauss4:
+        return bt ? xc::launch_gauss4_blocks(pl, *bt, n_blocks, F, N, o, accumulate, s, in)
+                  : xc::launch_gauss4(pl, v, T, F, N, o, accumulate, s, in);
+    default:
+        return bt ? xc::launch_mfma4f_blocks(pl, *bt, n_blocks, F, N, o, accumulate, s, in)
+                  : xc::launch_mfma4f(pl, v, T, F, N, o, accumulate, s, in);
     }
-    if (gauss_runs(ctx->k4, ctx->plan, F, N) && (uintptr_t)v % 16 == 0)
-        return xc::launch_gauss4(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
-    return xc::launch_mfma4f(ctx->plan, v, T, F, N, out, accumulate, s, acc_in);
 }
 
 // Whether a member of a batch is launched by itself: the kernel for its size
@@ -292,28 +334,15 @@ hipError_t launch4(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, int2 *out,
 // 198; 512 x 128 + 16 x 8, 2048 samples 195 and 172.  One triangle of 129 to 192
 // inputs gains from about 1024 samples on (192 x 256 twice, 64 samples 48 and
 // 53), and with running sums nothing does (545 and 542 without the dumps).
-bool batch_alone(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, bool accumulate)
+// A member whose tile was named, or tuned for the batched kernel, stays in the
+// shared launch.
+bool batch_alone(const xcorr_ctx *ctx, bool tuned, const uint8_t *v, int64_t T, bool accumulate)
 {
     const int F = ctx->cfg.n_chans, N = ctx->cfg.n_inputs;
-    if (accumulate || !free_choice(ctx) || N % 16 || (uintptr_t)v % 16 || !word_rows(ctx->cfg, v) ||
-        !xc::gauss4_runs(ctx->plan, F, N))
+    if (accumulate || tuned || ctx->tile_named || N % 16 || (uintptr_t)v % 16)
         return false;
-    return (xc::duo4_taken(N, T) && (int64_t)F * ((N + 127) / 128) >= 512) || (xc::tri48_taken(N) && F >= 256 && T >= 1024);
-}
-
-// One MFMA-path launch of either sample format (not the per-role kernel):
-// results to `out`, running sums (accumulate = 1) from acc_in.
-hipError_t launch_mfma(const xcorr_ctx *ctx, const uint8_t *v, int64_t T, void *out, int accumulate, hipStream_t s,
-                       const void *acc_in)
-{
-    const xcorr_config &c = ctx->cfg;
-    if (c.sample_bits == 4)
-        return launch4(ctx, v, T, static_cast<int2 *>(out), accumulate, s, static_cast<const int2 *>(acc_in));
-    // as for 4+4-bit launches, the library chooses unless the config names a tile
-    const bool f16 = c.path == XCORR_PATH_F16_MFMA;
-    const int rb = c.tile ? 0 : xc::split8_blocks(ctx->plan, f16, v, c.n_chans, c.n_inputs, T);
-    return rb ? xc::launch_split8(rb, f16, v, T, c.n_chans, c.n_inputs, out, acc_in, accumulate, s)
-              : xc::launch_mfma8(ctx->plan, f16, v, T, c.n_chans, c.n_inputs, out, acc_in, accumulate, s);
+    const Launch k = choose(ctx->cfg, ctx->plan, ctx->k4, false, v, T).kernel;
+    return (k == Launch::Duo4 && (int64_t)F * ((N + 127) / 128) >= 512) || (k == Launch::Tri48 && F >= 256 && T >= 1024);
 }
 
 // The current device must be a gfx950 GPU.
@@ -346,6 +375,7 @@ void setup_ctx(xcorr_ctx *c, const xcorr_config &cfg, int64_t tm, void *ws, size
             tile = cached_tile(cfg, false);
             c->tile_from_cache = tile != 0;
         }
+        c->tile_named = tile != 0;
         if (!tile)
             tile = default_tile(cfg.n_inputs);
         c->plan = xc::make_plan(cfg.n_inputs, tile);
@@ -395,6 +425,7 @@ int xc::correlate_once(const xcorr_config *cfg, void *ws, size_t ws_bytes, const
 struct xcorr_batch {
     std::vector<xcorr_ctx *> ctx;
     std::vector<xc::Plan> plan;
+    std::vector<char> tuned;   // the plan's tile came from a tune-cache line of the batched kernel
     int *queue;
     int grid;   // work-groups of the queue-driven kernel: one per CU
 };
@@ -462,10 +493,8 @@ int xcorr_ingest(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, uint64_
         hipError_t e;
         if (c.path == XCORR_PATH_PLAIN)
             e = xc::launch_plain(c.sample_bits, vp, tl, c.n_chans, c.n_inputs, acc, accumulate, s);
-        else if (c.sample_bits == 4 && ctx->k4 == Kernel4::Roles)
-            e = xc::launch_mfma4(ctx->plan, ctx->kc, vp, tl, c.n_chans, c.n_inputs, acc, accumulate, s);
         else
-            e = launch_mfma(ctx, vp, tl, acc, accumulate, s, acc);
+            e = launch_mfma(ctx, vp, nullptr, 0, tl, acc, accumulate, s, acc);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
         ++ctx->launches;
@@ -500,7 +529,7 @@ int xcorr_ingest_dump(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, ui
         const bool last = t0 + tl >= n_samples;
         // the last launch adds the running sums to its own and writes the
         // result to d_out: the integration ends without a copy
-        const hipError_t e = launch_mfma(ctx, v + t0 * bytes_per_row, tl, last ? d_out : ctx->ws, accumulate, s,
+        const hipError_t e = launch_mfma(ctx, v + t0 * bytes_per_row, nullptr, 0, tl, last ? d_out : ctx->ws, accumulate, s,
                                          ctx->ws);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
@@ -554,18 +583,7 @@ int xcorr_ingest_blocks(xcorr_ctx *ctx, const void *const *d_blocks, int n_block
             bt.p[b] = static_cast<const uint8_t *>(d_blocks[b0 + b]);
         bt.chunks_per_block = (int)(block_samples / 64);
         const int accumulate = (ctx->acc_samples > 0 || b0 > 0) ? 1 : 0;
-        const bool gauss = gauss_runs(ctx->k4, ctx->plan, c.n_chans, c.n_inputs);
-        const bool choose = gauss && free_choice(ctx);
-        const int F = c.n_chans, N = c.n_inputs;
-        const int64_t T = n * block_samples;
-        int2 *const acc = static_cast<int2 *>(ctx->ws);
-        const int rb = choose ? xc::split4_blocks(ctx->plan, F, N, T) : 0;
-        const hipError_t e =
-            rb                               ? xc::launch_split4_blocks(rb, bt, n, F, N, acc, accumulate, s)
-            : choose && xc::duo4_taken(N, T) ? xc::launch_duo4(bt.p[0], &bt, T, F, N, acc, acc, accumulate, s)
-            : choose && xc::tri48_taken(N)   ? xc::launch_tri48(bt.p[0], &bt, T, F, N, acc, acc, accumulate, s)
-            : gauss                          ? xc::launch_gauss4_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s)
-                                             : xc::launch_mfma4f_blocks(ctx->plan, bt, n, F, N, acc, accumulate, s);
+        const hipError_t e = launch_mfma(ctx, bt.p[0], &bt, n, n * block_samples, ctx->ws, accumulate, s, ctx->ws);
         if (e != hipSuccess)
             return hip_fail(e, "kernel launch");
         ++ctx->launches;
@@ -669,8 +687,10 @@ int xcorr_batch_init(xcorr_ctx *const *ctxs, int n, void *d_workspace, size_t ws
     if (!b)
         return set_error(XCORR_E_NOMEM, "host allocation failed");
     for (int a = 0; a < n; ++a) {
+        bool tuned = false;
         b->ctx.push_back(ctxs[a]);
-        b->plan.push_back(batch_plan(ctxs[a]));
+        b->plan.push_back(batch_plan(ctxs[a], &tuned));
+        b->tuned.push_back(tuned);
     }
     b->queue = static_cast<int *>(d_workspace);
     b->grid = cus;   // one 512-thread work-group per CU (LDS-limited), persistent
@@ -717,7 +737,7 @@ int xcorr_batch_ingest(xcorr_batch *b, const void *const *d_volts, const int64_t
             const xcorr_ctx *c = b->ctx[a];
             const xc::Plan &pl = b->plan[a];
             const int F = c->cfg.n_chans, N = c->cfg.n_inputs;
-            if (batch_alone(c, static_cast<const uint8_t *>(d_volts[a]) + t0 * (int64_t)F * N,
+            if (batch_alone(c, b->tuned[a], static_cast<const uint8_t *>(d_volts[a]) + t0 * (int64_t)F * N,
                             std::min(L, n_samples[a] - t0), c->acc_samples > 0 || t0 > 0)) {
                 alone[n_alone++] = a;
                 continue;
@@ -749,8 +769,8 @@ int xcorr_batch_ingest(xcorr_batch *b, const void *const *d_volts, const int64_t
         for (int k = 0; k < n_alone && e == hipSuccess; ++k) {
             const xcorr_ctx *c = b->ctx[alone[k]];
             const int64_t row = (int64_t)c->cfg.n_chans * c->cfg.n_inputs;
-            e = launch4(c, static_cast<const uint8_t *>(d_volts[alone[k]]) + t0 * row,
-                        std::min(L, n_samples[alone[k]] - t0), static_cast<int2 *>(c->ws), 0, s);
+            e = launch_mfma(c, static_cast<const uint8_t *>(d_volts[alone[k]]) + t0 * row, nullptr, 0,
+                            std::min(L, n_samples[alone[k]] - t0), c->ws, 0, s, c->ws);
         }
         if (e == hipSuccess && args.n > 0)
             e = gauss ? xc::launch_gauss4_batch(args, b->grid, s)
@@ -819,6 +839,26 @@ int xcorr_autotune_kernel(const xcorr_config *cfg, int32_t batch, char *name, si
     if (!tile)
         tile = default_tile(cfg->n_inputs);
     std::snprintf(name, len, "%s", kernel_for(*cfg, tile, batch != 0));
+    return XCORR_OK;
+}
+
+int xcorr_ingest_kernel(const xcorr_config *cfg, const void *d_volts, int64_t n_samples, char *name, size_t len)
+{
+    const int rc = validate(cfg, nullptr);
+    if (rc)
+        return rc;
+    if (!name || len < 1)
+        return set_error(XCORR_E_INVAL, "name is NULL or empty");
+    if (n_samples < 1)
+        return set_error(XCORR_E_INVAL, "n_samples must be >= 1");
+    const char *k = "xc_plain_kernel";
+    if (cfg->path != XCORR_PATH_PLAIN) {
+        const int tile = cfg->tile ? cfg->tile : cached_tile(*cfg, false);
+        const xc::Plan pl = xc::make_plan(cfg->n_inputs, tile ? tile : default_tile(cfg->n_inputs));
+        const int64_t L = cfg->sample_bits == 4 ? xc::kMaxSamplesPerLaunch4 : xc::kMaxSamplesPerLaunch8;
+        k = launch_name(*cfg, choose(*cfg, pl, kernel4_from_env(), tile != 0, d_volts, std::min(n_samples, L)).kernel);
+    }
+    std::snprintf(name, len, "%s", k);
     return XCORR_OK;
 }
 

@@ -149,6 +149,7 @@ def load(path: str | None = None):
             "xcorr_autotune": [cfgp, vp, sz, vp, ctypes.POINTER(ctypes.c_int32)],
             "xcorr_autotune_batch": [cfgp, vp, sz, vp, ctypes.POINTER(ctypes.c_int32)],
             "xcorr_autotune_kernel": [cfgp, ctypes.c_int32, ctypes.c_char_p, sz],
+            "xcorr_ingest_kernel": [cfgp, vp, ctypes.c_int64, ctypes.c_char_p, sz],
             "xcorr_plan_tile": [cfgp, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32),
                                 ctypes.POINTER(ctypes.c_int32)],
             "xcorr_correlate_static": [cfgp, vp, i64, vp, ctypes.POINTER(i64), vp],
@@ -350,6 +351,16 @@ def xcorr_autotune_kernel(cfg: Config, batch: bool = False) -> str:
     """Name of the kernel the tuner times for this config (the one it runs)."""
     buf = ctypes.create_string_buffer(96)
     _check(load().xcorr_autotune_kernel(ctypes.byref(cfg), int(batch), buf, len(buf)), "xcorr_autotune_kernel")
+    return buf.value.decode()
+
+
+def xcorr_ingest_kernel(cfg: Config, volts, n_samples: int) -> str:
+    """The kernel that xcorr_ingest of these samples launches first.  volts: a
+    tensor, or the address whose alignment counts."""
+    buf = ctypes.create_string_buffer(64)
+    ptr = volts if isinstance(volts, int) else volts.data_ptr()
+    _check(load().xcorr_ingest_kernel(ctypes.byref(cfg), ctypes.c_void_p(ptr), n_samples, buf, len(buf)),
+           "xcorr_ingest_kernel")
     return buf.value.decode()
 
 

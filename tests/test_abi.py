@@ -223,3 +223,59 @@ def test_tune_cache_lines_are_used_only_for_their_kernel(tmp_path, monkeypatch):
     assert X.xcorr_plan_tile(X.make_config(160, 8, 4, X.PATH_I8_MFMA, tile=5), batch=True)[0] in (2, 3, 4)
     monkeypatch.delenv("XCORR_TUNE_CACHE")
     assert X.xcorr_plan_tile(cfg) == (6, False)
+
+
+def test_ingest_kernel_follows_size_and_alignment(monkeypatch):
+    """With neither a tile nor a tune-cache line the library picks a kernel by
+    size, format and alignment; a named tile runs the kernel the tuner times."""
+    monkeypatch.delenv("XCORR_MFMA4_VARIANT", raising=False)
+    monkeypatch.delenv("XCORR_TUNE_CACHE", raising=False)
+
+    def kernel(N, F, T, bits=4, path=X.PATH_I8_MFMA, tile=0, at=256):
+        return X.xcorr_ingest_kernel(X.make_config(N, F, bits, path, tile=tile), at, T)
+
+    assert kernel(192, 1024, 4096) == "xc_tri48_kernel"
+    assert kernel(192, 1024, 4096, at=260) == "xc_tri48_kernel"      # rows on 4-byte boundaries
+    assert kernel(192, 1024, 4096, at=257) == "xc_split_kernel"
+    assert kernel(192, 32, 4096) == "xc_split_kernel"                # few channels
+    assert kernel(128, 512, 4096) == kernel(512, 512, 2048) == kernel(100, 512, 1000) == "xc_duo4_kernel"
+    assert kernel(512, 512, 65_473) == "xc_gauss4_kernel"            # past duo4's int32 bound
+    assert kernel(96, 2048, 1024) == kernel(64, 4096, 2048) == "xc_gauss4_kernel"
+    assert kernel(99, 512, 1000) == "xc_split_kernel"
+    assert kernel(99, 512, 100) == "xc_mfma4f_kernel"
+    assert kernel(192, 1024, 4096, path=X.PATH_PLAIN) == "xc_plain_kernel"
+    assert kernel(192, 512, 8192, 8) == "xc_mfma8_kernel_i8"
+    assert kernel(192, 512, 8192, 8, X.PATH_F16_MFMA) == "xc_mfma8_kernel_f16"
+    assert kernel(192, 32, 8192, 8) == kernel(192, 32, 8192, 8, X.PATH_F16_MFMA) == "xc_split_kernel"
+    for N, F, tile, want in ((192, 1024, 6, "xc_gauss4_kernel"), (192, 32, 4, "xc_gauss4_kernel"),
+                             (512, 512, 4, "xc_gauss4_kernel"), (100, 512, 4, "xc_mfma4f_kernel")):
+        assert kernel(N, F, 1000, tile=tile) == want == X.xcorr_autotune_kernel(X.make_config(N, F, tile=tile))
+    assert kernel(192, 32, 8192, 8, tile=6) == "xc_mfma8_kernel_i8"
+    monkeypatch.setenv("XCORR_MFMA4_VARIANT", "fused")
+    assert kernel(192, 1024, 4096) == "xc_mfma4f_kernel"
+    monkeypatch.setenv("XCORR_MFMA4_VARIANT", "roles")
+    assert kernel(192, 1024, 4096) == "xc_mfma4_kernel"
+    for bad in (dict(T=0), dict(N=0)):
+        with pytest.raises(X.XcorrError):
+            kernel(**{**dict(N=192, F=8, T=64), **bad})
+
+
+@pytest.mark.parametrize("N,F,bits,path,tile", [(192, 1024, 4, X.PATH_I8_MFMA, 4), (192, 32, 4, X.PATH_I8_MFMA, 6),
+                                                (128, 512, 4, X.PATH_I8_MFMA, 2), (100, 512, 4, X.PATH_I8_MFMA, 3),
+                                                (60, 512, 4, X.PATH_I8_MFMA, 3), (192, 32, 8, X.PATH_I8_MFMA, 6),
+                                                (33, 64, 8, X.PATH_F16_MFMA, 2)])
+def test_a_tuned_tile_runs_on_the_kernel_it_was_timed_on(tmp_path, monkeypatch, N, F, bits, path, tile):
+    """A context that takes its tile from a tune-cache line launches the kernel
+    named in that line, whatever the library would choose by size."""
+    monkeypatch.delenv("XCORR_MFMA4_VARIANT", raising=False)
+    cfg = X.make_config(N, F, bits, path)
+    timed = X.xcorr_autotune_kernel(X.make_config(N, F, bits, path, tile=tile))
+    monkeypatch.delenv("XCORR_TUNE_CACHE", raising=False)
+    assert X.xcorr_ingest_kernel(cfg, 256, 2048) != timed or N == 60
+    cache = tmp_path / "tune.txt"
+    cache.write_text(f"{bits} {N} {F} {path} {tile} {timed}\n")
+    monkeypatch.setenv("XCORR_TUNE_CACHE", str(cache))
+    assert X.xcorr_plan_tile(cfg) == (tile, True)
+    assert X.xcorr_autotune_kernel(cfg) == timed
+    for T in (64, 2048, 8192):
+        assert X.xcorr_ingest_kernel(cfg, 256, T) == timed
