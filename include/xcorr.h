@@ -168,8 +168,9 @@ int xcorr_dump(xcorr_ctx *ctx, void *d_out, int64_t *n_integrated, uint64_t *n_g
  * xcorr_ingest(ctx, d_volts, n_samples, seq) followed by xcorr_dump(ctx,
  * d_out, ...), with the same results.  On the MFMA paths the final launch
  * adds the running sums to its own and writes the visibilities straight into
- * d_out (16-byte aligned), so no separate copy runs; the plain path makes the
- * two calls.  Errors as the two calls.
+ * d_out (16-byte aligned), so no separate copy runs; the plain path, and a
+ * d_out that overlaps the samples, make the two calls.  Errors as the two
+ * calls.
  */
 int xcorr_ingest_dump(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, uint64_t seq, void *d_out,
                       int64_t *n_integrated, uint64_t *n_gaps, void *stream);

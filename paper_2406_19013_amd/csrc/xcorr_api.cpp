@@ -515,7 +515,13 @@ int xcorr_ingest_dump(xcorr_ctx *ctx, const void *d_volts, int64_t n_samples, ui
     if ((uintptr_t)d_out % 16)
         return set_error(XCORR_E_INVAL, "d_out must be 16-byte aligned");
     const xcorr_config &c = ctx->cfg;
-    if (c.path == XCORR_PATH_PLAIN || (c.sample_bits == 4 && ctx->k4 == Kernel4::Roles)) {
+    // Two calls where no kernel does both, and where d_out overlaps the samples
+    // (a caller that dumps into the block it has just handed over): a launch
+    // that writes d_out may still have samples to read.
+    const size_t acc = acc_bytes(c), in = (size_t)n_samples * c.n_chans * c.n_inputs * (c.sample_bits == 4 ? 1 : 2);
+    const bool overlap = (uintptr_t)d_out < (uintptr_t)d_volts + in && (uintptr_t)d_volts < (uintptr_t)d_out + acc;
+    if (c.path == XCORR_PATH_PLAIN || (c.sample_bits == 4 && ctx->k4 == Kernel4::Roles) ||
+        (overlap && ctx->ws_bytes >= acc)) {
         const int rc = xcorr_ingest(ctx, d_volts, n_samples, seq, stream);
         return rc ? rc : xcorr_dump(ctx, d_out, n_integrated, n_gaps, stream);
     }

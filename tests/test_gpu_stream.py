@@ -240,3 +240,38 @@ def test_calls_go_to_the_current_stream():
         assert X._stream_handle(None) == side.cuda_stream
     assert X._stream_handle(None) == (torch.cuda.current_stream().cuda_stream or None)
     assert X._stream_handle(side) == side.cuda_stream and X._stream_handle(0) is None
+
+
+@pytest.mark.parametrize("bits,path", [(4, X.PATH_I8_MFMA), (8, X.PATH_I8_MFMA), (8, X.PATH_F16_MFMA)],
+                         ids=["4bit", "8bit", "8bit_f16"])
+@pytest.mark.parametrize("first", [0, 4096, -1])
+def test_dump_into_the_block_it_ends_with(bits, path, first):
+    """A dump buffer that overlaps the integration's last block (at its start,
+    inside it, over its end): the block is read before the dump is written, as
+    by an ingest and a dump, in a context's call and in a pipe."""
+    N, F, T = 100, 300, 700
+    P = N * (N + 1) // 2
+    _say(f"dump into the block {bits} bits path {path} at {first}")
+    v = (synth.uniform_volts4 if bits == 4 else synth.uniform_volts8)(N, F, T, seed=(4010, bits), device="cuda")
+    ref = X.Correlator(N, F, bits, X.PATH_PLAIN)
+    want, _, _ = ref.ingest_dump(v)
+    ref.close()
+    nbytes = v.numel() * v.element_size()
+    at = first if first >= 0 else nbytes // 16 * 16 - 4096
+    raw = torch.empty(nbytes + F * P * 8, dtype=torch.uint8, device="cuda")
+    out = raw[at:at + F * P * 8].view(torch.float32 if path == X.PATH_F16_MFMA else torch.int32).view(F, P, 2)
+    block = raw[:nbytes].view(v.dtype).view(v.shape)
+    c = X.Correlator(N, F, bits, path)
+    p = X.Pipe(c, T, 2, host_blocks=False)
+    for scale in (1, 2):
+        block.copy_(v)
+        if scale == 1:
+            c.ingest_dump(block, out)
+        else:
+            p.push(v)
+            assert p.push(block, out)
+            p.drain()
+        torch.cuda.synchronize()
+        assert torch.equal(out.to(torch.int64), scale * want.to(torch.int64)), scale
+    p.close()
+    c.close()
