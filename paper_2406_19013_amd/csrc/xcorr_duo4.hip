@@ -108,6 +108,7 @@ constexpr DuoProduct duo_product(int SH, int ROLE, int k)
 struct DuoArgs {
     int64_t T;        // samples (MB = 1: whole blocks)
     int F, N;
+    int f0, nf;       // channels of this launch
     int ntri, nrect;  // triangles and rectangles per channel
     int2 *out;        // [F][P] results
     const int2 *in;   // [F][P] running sums (ACC = 1)
@@ -160,8 +161,8 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     lds_u8 *const ring = (lds_u8 *)smem;
 
     const int xcd = blockIdx.x & 7, m = (int)(blockIdx.x >> 3), M = gridDim.x >> 3;
-    const int per = (a.F * nreg + 7) / 8, first = xcd * per;   // this XCD's items (channel, region)
-    const int rlen = min(per, a.F * nreg - first);
+    const int per = (a.nf * nreg + 7) / 8, first = xcd * per;   // this XCD's items (channel, region)
+    const int rlen = min(per, a.nf * nreg - first);
     const int n_my = rlen > m ? (rlen - m + M - 1) / M : 0;
     const int nch = (int)((a.T + C - 1) / C);
     const int total = n_my * nch;
@@ -190,9 +191,9 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     int is_k = 0, is_c = 0, issued = 0, islot = 0;
     int voff[LOADS];
     auto set_item = [&](int k) {
-        const int it = first + m + k * M, f = it / nreg;
+        const int it = first + m + k * M, c = it / nreg, f = a.f0 + c;
         int sa, sb;
-        segments(it - f * nreg, sa, sb);
+        segments(it - c * nreg, sa, sb);
         int ln = __lane_id();                 // recomputed per item: kept, these values would take
         asm volatile("" : "+v"(ln));          // the K loop's registers
 #pragma unroll
@@ -319,9 +320,9 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     };
 
     auto epilogue = [&](int it) {
-        const int f = __builtin_amdgcn_readfirstlane(it / nreg);
+        const int c = __builtin_amdgcn_readfirstlane(it / nreg), f = a.f0 + c;
         int sa, sb;
-        segments(it - f * nreg, sa, sb);
+        segments(it - c * nreg, sa, sb);
         const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
         const int bytes = (int)(8 * P);
         // rows past input N - 1 lie past the end of the channel's triangle:
@@ -536,6 +537,16 @@ void xc_duo4_kernel(const uint8_t *__restrict__ volts, const DuoArgs a, const Bl
 // padding.
 bool duo4_taken(int N, int64_t T) { return (N > 192 || (N > 96 && N <= 128)) && T <= kMaxSamplesDuo4; }
 
+// A launch of more than about 2 ms goes as two, each over half of the channels:
+// its work-groups hold every compute unit to its end, and another stream's
+// kernel waits for that.  96, 192 and 512 inputs x 4096 channels streaming side
+// by side: the 192-input array's p99 per block of 1024 samples 4.13 -> 2.28 ms
+// (2.98 when triangles and rectangles were a launch each), per group of 8 blocks
+// 19.3 -> 10.8 (15.3); the 512-input array's 4.19 -> 4.54 (4.62) and 19.4 -> 21.3
+// (23.2).  By itself the 512-input launch gains, as fewer channels are under way
+// at once (3410 -> 3375 us, 8 blocks 16,300 -> 15,700).
+static int duo4_launches(int64_t T, int F, int regions) { return F > 1 && T * F * regions >= 30000000 ? 2 : 1; }
+
 hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                        int accumulate, hipStream_t s)
 {
@@ -545,16 +556,23 @@ hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, in
     const int nseg = (N + 127) / 128, pairs = nseg * (nseg - 1) / 2;
     if ((int64_t)F * std::max(nseg, pairs) > (1LL << 30))
         return hipErrorInvalidValue;
-    const DuoArgs a{T, F, N, nseg, pairs, out, in};
-    const int per = (int)(((int64_t)F * std::max(nseg, pairs) + 7) / 8);
-    const int grid = 8 * std::max(1, std::min(compute_units() / 4, per));   // two per compute unit
     BlockTable table{};
     if (bt)
         table = *bt;
     auto kern = bt ? (accumulate ? xc_duo4_kernel<1, 1> : xc_duo4_kernel<0, 1>)
                    : (accumulate ? xc_duo4_kernel<1, 0> : xc_duo4_kernel<0, 0>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts, a, table);
-    return hipGetLastError();
+    const int launches = duo4_launches(T, F, nseg + pairs);
+    for (int k = 0; k < launches; ++k) {
+        const int f0 = (int)((int64_t)F * k / launches), nf = (int)((int64_t)F * (k + 1) / launches) - f0;
+        const DuoArgs a{T, F, N, f0, nf, nseg, pairs, out, in};
+        const int per = (int)(((int64_t)nf * std::max(nseg, pairs) + 7) / 8);
+        const int grid = 8 * std::max(1, std::min(compute_units() / 4, per));   // two per compute unit
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts, a, table);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace xc

@@ -116,3 +116,27 @@ def test_batch_members_launched_by_themselves(T):
             assert n == 2 * T and c.stats()["kernel_launches"] == 3
             assert torch.equal(out, 2 * _run(v, N, F, [T], X.PATH_PLAIN)), (N, F)
         b.close()
+
+
+@pytest.mark.parametrize("N,F,T", [(512, 601, 5056), (260, 1001, 5056)])
+def test_long_launches_in_two(N, F, T):
+    """Channels of an odd count in two launches: stored, added, from a block
+    table and dumped, against the three-product kernel."""
+    print(f"two launches N={N} F={F} T={T}", flush=True)
+    v = synth.uniform_volts4(N, F, T, seed=(2306, N), device="cuda")
+    assert X.xcorr_ingest_kernel(X.make_config(N, F), v, T) == "xc_duo4_kernel"
+    ref = X.Correlator(N, F, tile=4)
+    want, _, _ = ref.ingest_dump(v)
+    ref.close()
+    c = X.Correlator(N, F)
+    out, _, _ = c.ingest_dump(v)
+    assert torch.equal(out, want)
+    c.ingest(v)
+    out, _, _ = c.ingest_dump(v)
+    assert torch.equal(out, 2 * want)
+    if N % 16 == 0:
+        c.ingest_blocks([v, v])
+        out, _, _ = c.dump()
+        assert torch.equal(out, 2 * want)
+    torch.cuda.synchronize()
+    c.close()
