@@ -240,8 +240,8 @@ int xcorr_batch_destroy(xcorr_batch *b);
  * neither a tile nor a line the library chooses the kernel of each launch by
  * its size, also among kernels that take no tile and are often faster than
  * every tile: xcorr_ingest_kernel (pure host) names the one that the first
- * launch of xcorr_ingest(d_volts, n_samples) runs in a context of this config
- * (d_volts counts by its alignment only).  xcorr_plan_tile (pure host) reports
+ * launch of an integration, xcorr_ingest(d_volts, n_samples), runs in a context
+ * of this config (d_volts counts by its alignment only).  xcorr_plan_tile (pure host) reports
  * the tile xcorr_init (batch = 0) or xcorr_batch_init (batch = 1) would use
  * and whether it came from the cache.  The tuners block until their timing
  * runs on `stream` have finished.  xcorr_autotune_query gives the scratch

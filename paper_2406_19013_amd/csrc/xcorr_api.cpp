@@ -120,8 +120,9 @@ struct Choice {
 // 16-byte-aligned blocks that starts with v).  named: the tile was named, by
 // the config or by a tune-cache line, and the kernels that take tiles run with
 // that plan, as the tuner timed them; otherwise (or with the environment naming
-// another 4+4-bit family) the library chooses by size and alignment.
-Choice choose(const xcorr_config &c, const xc::Plan &pl, Kernel4 k4, bool named, const void *v, int64_t T)
+// another 4+4-bit family) the library chooses by size, alignment and whether the
+// launch adds to running sums.
+Choice choose(const xcorr_config &c, const xc::Plan &pl, Kernel4 k4, bool named, const void *v, int64_t T, bool adds)
 {
     const int F = c.n_chans, N = c.n_inputs;
     if (c.sample_bits == 8) {
@@ -135,7 +136,9 @@ Choice choose(const xcorr_config &c, const xc::Plan &pl, Kernel4 k4, bool named,
             if (xc::gauss4_runs(pl, F, N)) {
                 if (const int rb = xc::split4_blocks(pl, F, N, T))
                     return {Launch::Split4, rb};
-                return {xc::duo4_taken(N, T) ? Launch::Duo4 : xc::tri48_taken(N) ? Launch::Tri48 : Launch::Gauss4};
+                return {xc::duo4_taken(N, F, T, adds) ? Launch::Duo4
+                        : xc::tri48_taken(N, F, T)  ? Launch::Tri48
+                                                    : Launch::Gauss4};
             }
         } else if (xc::split4_unaligned(F, N, T)) {
             return {Launch::Split4, 1};
@@ -169,7 +172,7 @@ const char *kernel_for(const xcorr_config &c, int tile, bool batch)
         return kernel4_from_env() == Kernel4::Gauss && xc::gauss4_batch_shape(pl, c.n_chans, c.n_inputs)
                    ? "xc_gauss4_batch_kernel"
                    : "xc_batch4_kernel";
-    return launch_name(c, choose(c, pl, kernel4_from_env(), true, nullptr, 1).kernel);
+    return launch_name(c, choose(c, pl, kernel4_from_env(), true, nullptr, 1, false).kernel);
 }
 
 // Tiles the batched kernel carries for an array of N inputs.
@@ -306,7 +309,7 @@ hipError_t launch_mfma(const xcorr_ctx *ctx, const void *input, const xc::BlockT
     const int F = c.n_chans, N = c.n_inputs;
     const bool f16 = c.path == XCORR_PATH_F16_MFMA;
     const uint8_t *v = static_cast<const uint8_t *>(input);
-    const Choice k = choose(c, pl, ctx->k4, ctx->tile_named, v, T);
+    const Choice k = choose(c, pl, ctx->k4, ctx->tile_named, v, T, accumulate);
     int2 *const o = static_cast<int2 *>(out);
     const int2 *const in = static_cast<const int2 *>(acc_in);
     switch (k.kernel) {
@@ -341,7 +344,7 @@ bool batch_alone(const xcorr_ctx *ctx, bool tuned, const uint8_t *v, int64_t T, 
     const int F = ctx->cfg.n_chans, N = ctx->cfg.n_inputs;
     if (accumulate || tuned || ctx->tile_named || N % 16 || (uintptr_t)v % 16)
         return false;
-    const Launch k = choose(ctx->cfg, ctx->plan, ctx->k4, false, v, T).kernel;
+    const Launch k = choose(ctx->cfg, ctx->plan, ctx->k4, false, v, T, false).kernel;
     return (k == Launch::Duo4 && (int64_t)F * ((N + 127) / 128) >= 512) || (k == Launch::Tri48 && F >= 256 && T >= 1024);
 }
 
@@ -862,7 +865,7 @@ int xcorr_ingest_kernel(const xcorr_config *cfg, const void *d_volts, int64_t n_
         const int tile = cfg->tile ? cfg->tile : cached_tile(*cfg, false);
         const xc::Plan pl = xc::make_plan(cfg->n_inputs, tile ? tile : default_tile(cfg->n_inputs));
         const int64_t L = cfg->sample_bits == 4 ? xc::kMaxSamplesPerLaunch4 : xc::kMaxSamplesPerLaunch8;
-        k = launch_name(*cfg, choose(*cfg, pl, kernel4_from_env(), tile != 0, d_volts, std::min(n_samples, L)).kernel);
+        k = launch_name(*cfg, choose(*cfg, pl, kernel4_from_env(), tile != 0, d_volts, std::min(n_samples, L), false).kernel);
     }
     std::snprintf(name, len, "%s", k);
     return XCORR_OK;

@@ -145,13 +145,13 @@ hipError_t launch_split4_blocks(int rb, const BlockTable &bt, int n_blocks, int 
 // (rows on 4-byte boundaries; with a block table, blocks of 64-sample chunks),
 // and the rule that takes it.
 constexpr int64_t kMaxSamplesDuo4 = 65472;   // int32 accumulators of 2^15 per sample
-bool duo4_taken(int N, int64_t T);
+bool duo4_taken(int N, int F, int64_t T, bool adds);   // adds: to running sums
 hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                        int accumulate, hipStream_t s);
 
 // 4+4-bit kernel for one triangle of 129 to 192 inputs, as four segments of
 // 48 (same operands), and its rule.
-bool tri48_taken(int N);
+bool tri48_taken(int N, int F, int64_t T);
 hipError_t launch_tri48(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                         int accumulate, hipStream_t s);
 

@@ -546,14 +546,14 @@ int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
     const bool pairs = c.pairs && pl.D >= 2 && pl.D <= 4 && F >= 2;
     const double tri_items = (pairs ? (F + 1) / 2 : F) * (double)pl.nseg, rect_items = F * (double)(pl.regions - pl.nseg);
     double other;
-    if (c.four_bit && duo4_taken(N, T)) {
+    if (c.four_bit && duo4_taken(N, F, T, true)) {
         // two work-groups per compute unit: below half a load a round takes
         // its least time; results are written at about 5 TB/s
         const double nseg = (N + 127) / 128, tri = F * nseg, rect = tri * (nseg - 1) / 2;
         other = 4.5 + t * std::max(0.0068, 0.0168 * tri / 512.0) + 0.0132 * tri;
         if (rect > 0)
             other += 5.7 + t * std::max(0.0115, 0.0185 * rect / 512.0) + 0.026 * rect;
-    } else if (c.four_bit && tri48_taken(N)) {
+    } else if (c.four_bit && tri48_taken(N, F, T)) {
         other = std::ceil(F / 256.0) * (6.0 + 0.0105 * t);
     } else if (c.one_launch && pl.nseg > 1)
         other = std::ceil((tri_items + rect_items) / 256.0) * (c.rect_fixed + c.rect_chunk * t);

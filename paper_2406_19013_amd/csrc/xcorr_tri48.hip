@@ -337,7 +337,7 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
     }
     wait_vmcnt_chunks<kTsLoads, kTsRing - 1>(kTsRing - 1);
     barrier_no_fence();
-    // operands of a channel's first step
+    // operands of the stream's first step
     auto begin = [&](lds_u8 *p) {
         if constexpr (TRI) {
             static_for<0, 6>([&](auto k) { read(p, k); });
@@ -374,8 +374,8 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
             issue_open();
         };
         // A step of 64 samples.  Half blocks are unpacked in place once their
-        // last product of a step is issued (past a channel's or the stream's
-        // end what is read and unpacked ahead is not used).
+        // last product of a step is issued (past a channel's end what is read
+        // and unpacked ahead is the next one's).
         static_for<0, 2>([&](auto s) {
             lds_u8 *const qn = s ? pn : p + 64 * kTsRow;
             if constexpr (TRI) {
@@ -441,7 +441,6 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
             stored_after = issued;
             ++ck;
             clear();
-            begin(pn);
         }
     }
 }
@@ -469,7 +468,10 @@ void xc_tri48_kernel(const uint8_t *__restrict__ volts, const TsArgs a, const Bl
 // work there): 132 inputs x 512 channels x 2048 samples 62 and 76, x 64 channels
 // 28 and 30; 192 x 256 x 1024 26.6 and 26.2.  Below 129 inputs the triangles of
 // up to four blocks are smaller than its padding; above 192 it has no regions.
-bool tri48_taken(int N) { return N > 128 && N <= 192; }
+// A launch of at most half a slot leaves it behind the three-product kernel
+// (192 x 1024 x 64 34.2 and 30.8, x 128 35.0 and 34.1; 160 x 512 x 64 17.1 and
+// 15.2) until the results are what takes the time (192 x 4096 x 64 176 and 180).
+bool tri48_taken(int N, int F, int64_t T) { return N > 128 && N <= 192 && (T > 64 || F > 2048); }
 
 hipError_t launch_tri48(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                         int accumulate, hipStream_t s)
