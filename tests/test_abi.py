@@ -282,3 +282,21 @@ def test_a_tuned_tile_runs_on_the_kernel_it_was_timed_on(tmp_path, monkeypatch, 
     assert X.xcorr_autotune_kernel(cfg) == timed
     for T in (64, 2048, 8192):
         assert X.xcorr_ingest_kernel(cfg, 256, T) == timed
+
+
+def test_full_rounds_of_unaligned_triangles_stay_with_the_fused_kernel(monkeypatch):
+    """Rows off the 4-byte boundaries, 65 to 192 inputs: with full rounds of 256
+    work-groups and a few hundred samples the time-split kernel is the slower
+    (161 x 256 x 160: 29 against 23 us)."""
+    monkeypatch.delenv("XCORR_MFMA4_VARIANT", raising=False)
+    monkeypatch.delenv("XCORR_TUNE_CACHE", raising=False)
+
+    def kernel(N, F, T):
+        return X.xcorr_ingest_kernel(X.make_config(N, F), 256, T)
+
+    for N, F, T in ((161, 256, 160), (161, 512, 200), (161, 700, 160), (191, 256, 160), (129, 256, 200), (65, 256, 64),
+                    (95, 256, 64)):
+        assert kernel(N, F, T) == "xc_mfma4f_kernel", (N, F, T)
+    for N, F, T in ((161, 100, 160), (161, 300, 160), (161, 256, 600), (191, 256, 450), (129, 512, 450), (65, 340, 64),
+                    (95, 256, 100), (99, 512, 1000), (63, 256, 64), (193, 256, 160)):
+        assert kernel(N, F, T) == "xc_split_kernel", (N, F, T)
