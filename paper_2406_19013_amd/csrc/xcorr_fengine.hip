@@ -627,16 +627,18 @@ int fe_cu_count()
 
 // Persistent grid: kFeWgsPerCu work-groups per compute unit, a multiple of 8
 // (one run of items per XCD), no more than there are items per XCD.  Two
-// spectra to an item once items of one would give some compute unit more than
-// one: an item of two costs about 1.6 of one.
+// spectra to an item where that takes less time: an item of two costs about 1.6
+// of one, and the work-groups take their items in rounds (4112 inputs, one
+// spectrum: two rounds either way, 28 us and 41 with two to an item; 192 x 22
+// spectra: two rounds and one, 33 and 24).
 template <class K1, class K2>
 hipError_t fe_launch(K1 one, K2 two, const FeArgs &a, hipStream_t s)
 {
     const int cus = fe_cu_count();
-    const int64_t groups = a.N / kFeGroup, pairs = ((int64_t)a.n_spectra + 1) / 2 * groups;
-    const bool both = a.n_spectra * groups > (int64_t)cus * kFeWgsPerCu;
-    const int64_t per_xcd = ((both ? pairs : a.n_spectra * groups) + 7) / 8;
-    const int grid = 8 * (int)std::max<int64_t>(1, std::min<int64_t>(cus / 8 * kFeWgsPerCu, per_xcd));
+    const int64_t groups = a.N / kFeGroup, wgs = cus / 8 * kFeWgsPerCu;   // work-groups per XCD
+    const int64_t singles = (a.n_spectra * groups + 7) / 8, pairs = (((int64_t)a.n_spectra + 1) / 2 * groups + 7) / 8;
+    const bool both = 8 * ((pairs + wgs - 1) / wgs) < 5 * ((singles + wgs - 1) / wgs);
+    const int grid = 8 * (int)std::max<int64_t>(1, std::min(wgs, both ? pairs : singles));
     if (both)
         hipLaunchKernelGGL(two, dim3(grid), dim3(kFeThreads), 0, s, a);
     else

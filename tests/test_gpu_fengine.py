@@ -204,3 +204,23 @@ def test_two_spectra_at_a_time(odd):
         torch.cuda.synchronize()
         assert np.array_equal(one.cpu().numpy(), got[m0:m0 + n])
         assert torch.equal(s1, spec[:, m0:m0 + n])
+
+
+@pytest.mark.parametrize("M", [1, 3])
+def test_more_groups_than_compute_units(M):
+    """One and three spectra of 257 input groups: an item of two spectra would
+    be half empty, or a round too many.  Codes equal those of calls on 16
+    inputs, byte for byte."""
+    N = 16 * (torch.cuda.get_device_properties(DEV).multi_processor_count + 1)
+    _say(f"many groups N={N} M={M}")
+    g = torch.Generator().manual_seed(310 + M)
+    adc = torch.randint(-60, 61, (N, (M + TAPS - 1) * P), generator=g, dtype=torch.int8).to(DEV)
+    gains = (torch.rand((N, F), generator=g) * 0.01).to(DEV)
+    h = _coeffs()
+    out = torch.empty((M, F, N), dtype=torch.uint8, device=DEV)
+    X.xcorr_fengine(adc, h, gains, out, M)
+    for i in (0, 16, N // 32 * 16, N - 16):
+        part = torch.empty((M, F, 16), dtype=torch.uint8, device=DEV)
+        X.xcorr_fengine(adc[i:i + 16].contiguous(), h, gains[i:i + 16].contiguous(), part, M)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, :, i:i + 16], part), i
