@@ -395,13 +395,13 @@ int xcorr_reorder_destroy(xcorr_reorder *r);
  * config's (0: the built-in choice; the tune cache is not read), followed by
  * one xcorr_ingest_dump(n_samples) into d_out, with no context, no workspace
  * and no allocation.  An integration that needs running sums (more samples
- * than one 4+4-bit int8-MFMA launch takes, 130,560, or any 8+8-bit or plain
- * integration) keeps them in a library-held device array of
- * XCORR_STATIC_SCRATCH_BYTES per GPU, held until the process ends; configs
- * whose sums (F*P*2*4 bytes, rounded up to 256) exceed it are refused with
+ * than one 4+4-bit int8-MFMA launch takes, 130,560, or any plain one) keeps
+ * them in a library-held device array of XCORR_STATIC_SCRATCH_BYTES per GPU,
+ * held until the process ends; such configs, and 8+8-bit ones, whose sums
+ * (F*P*2*4 bytes, rounded up to 256) exceed it are refused with
  * XCORR_E_NOMEM before anything is enqueued.  The first launch of an
  * integration overwrites the array, so nothing needs clearing; it keeps the
- * last call's contents.  Calls that overlap on one GPU (two streams, or two
+ * contents of the last call that used it.  Calls that overlap on one GPU (two streams, or two
  * host threads) share the array and race.  Errors: as xcorr_query and
  * xcorr_ingest_dump, XCORR_E_NOMEM as above, XCORR_E_HIP if the array's
  * address cannot be looked up.

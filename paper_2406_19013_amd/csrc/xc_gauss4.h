@@ -278,22 +278,6 @@ constexpr int g3_smem_bytes(int D) { return g3_ring_bytes<SH>(D) + g3_tr_bytes<S
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-// Wait until the chunk before the last r chunks a wave issued has arrived,
-// when `after` other memory operations were issued since that chunk as well
-// (operations complete in order; the counter holds at most 63).
-template <int LOADS, int MAXR, int AFTER>
-__device__ __forceinline__ void wait_vmcnt_chunks_after(int r)
-{
-    if constexpr (MAXR > 0) {
-        if (r >= MAXR)
-            wait_vmcnt<(LOADS * MAXR + AFTER < 63 ? LOADS * MAXR + AFTER : 63)>();
-        else
-            wait_vmcnt_chunks_after<LOADS, MAXR - 1, AFTER>(r);
-    } else {
-        wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
-    }
-}
-
 // A product, and an operand's unpacking, at their place in the source: the
 // empty statements keep the compiler from moving them past each other.
 __device__ __forceinline__ void mfma_in_order(v16i &acc, v4i a, v4i b)

@@ -124,6 +124,22 @@ __device__ __forceinline__ void wait_vmcnt_chunks(int r)
     }
 }
 
+// Wait until the chunk before the last r chunks a wave issued has arrived,
+// when AFTER other memory operations were issued since that chunk as well
+// (operations complete in order; the counter holds at most 63).
+template <int LOADS, int MAXR, int AFTER>
+__device__ __forceinline__ void wait_vmcnt_chunks_after(int r)
+{
+    if constexpr (MAXR > 0) {
+        if (r >= MAXR)
+            wait_vmcnt<(LOADS * MAXR + AFTER < 63 ? LOADS * MAXR + AFTER : 63)>();
+        else
+            wait_vmcnt_chunks_after<LOADS, MAXR - 1, AFTER>(r);
+    } else {
+        wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
+    }
+}
+
 // The same pointer, in scalar registers: a buffer descriptor that the compiler
 // holds in vector registers costs a loop around every access.
 __device__ __forceinline__ const uint8_t *uniform_pointer(const uint8_t *p)

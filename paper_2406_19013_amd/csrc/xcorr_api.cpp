@@ -395,9 +395,9 @@ void setup_ctx(xcorr_ctx *c, const xcorr_config &cfg, int64_t tm, void *ws, size
 }  // namespace
 
 // One integration of n_samples through a context that lives on this stack
-// frame, with `ws` (ws_bytes) as its running-sum buffer when the integration
-// needs one: a single 4+4-bit int8-MFMA launch writes straight to d_out, any
-// other integration runs through the buffer.  Allocates nothing.
+// frame, with `ws` (ws_bytes) as its running-sum buffer.  A single 4+4-bit
+// int8-MFMA launch writes straight to d_out and may come with a buffer that is
+// too small; any other integration is refused with one.  Allocates nothing.
 int xc::correlate_once(const xcorr_config *cfg, void *ws, size_t ws_bytes, const void *d_volts, int64_t n_samples,
                        void *d_out, int64_t *n_integrated, hipStream_t s)
 {

@@ -116,22 +116,6 @@ struct DuoArgs {
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-// Wait until the chunk before the last r chunks a wave issued has arrived,
-// when AFTER other memory operations were issued since that chunk as well (the
-// counter holds at most 63).
-template <int LOADS, int MAXR, int AFTER>
-__device__ __forceinline__ void duo_wait(int r)
-{
-    if constexpr (MAXR > 0) {
-        if (r >= MAXR)
-            wait_vmcnt<(LOADS * MAXR + AFTER < 63 ? LOADS * MAXR + AFTER : 63)>();
-        else
-            duo_wait<LOADS, MAXR - 1, AFTER>(r);
-    } else {
-        wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
-    }
-}
-
 // A product at its place in the source: the empty statement keeps the compiler
 // from moving it past the unpacking written around it.
 __device__ __forceinline__ void fma_in_order(v16i &acc, v4i a, v4i b)
@@ -431,7 +415,7 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
             if (more) {
                 const int r = issued - 2 - c;
                 if (c + 1 < stored_after)
-                    duo_wait<LOADS, NBUF - 1, STORES>(r);
+                    wait_vmcnt_chunks_after<LOADS, NBUF - 1, STORES>(r);
                 else
                     wait_vmcnt_chunks<LOADS, NBUF - 1>(r);
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

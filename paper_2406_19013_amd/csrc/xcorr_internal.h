@@ -39,12 +39,6 @@ bool plan_supported(int N, int D);
 int correlate_once(const xcorr_config *cfg, void *ws, size_t ws_bytes, const void *d_volts, int64_t n_samples,
                    void *d_out, int64_t *n_integrated, hipStream_t s);
 
-// Launchers: enqueue on `stream`, return hipSuccess or the launch error.
-// `accumulate` = 0 overwrites the accumulators, 1 adds to them.
-// T <= kMaxSamplesPerLaunch for the MFMA paths (the host splits longer ingests).
-// 4+4-bit: the fused-product kernel keeps two K-parity partial sums of at
-// most 32896 per sample each (|256 Im| + |16 re|), over 32-sample steps, so a
-// launch takes at most 2 * 32 * floor((2^31 - 1) / 32896 / 32) samples.
 // compute units of the current device (queried once per device)
 inline int compute_units()
 {
@@ -61,9 +55,27 @@ inline int compute_units()
     return cus;
 }
 
+// Launchers: enqueue on `stream`, return hipSuccess or the launch error.
+// `accumulate` = 0 overwrites the accumulators, 1 adds to them.
+// T <= kMaxSamplesPerLaunch for the MFMA paths (the host splits longer ingests).
+// 4+4-bit: the fused-product kernel keeps two K-parity partial sums of at
+// most 32896 per sample each (|256 Im| + |16 re|), over 32-sample steps, so a
+// launch takes at most 2 * 32 * floor((2^31 - 1) / 32896 / 32) samples.  The
+// other kernels that go by this limit hold less: the three-product kernels (one
+// of them for 129 to 192 inputs) R_i R_j^T, 2^14 per sample, and beside it sums
+// that may wrap, of which 32 Im and 2 Re, at most 2^12 per sample, are taken; the
+// time-split kernel 2^15 per sample over an eighth of the samples and one step.
+// The kernel for 128-input segments holds 2^15 per sample over all of them.
 constexpr int64_t kMaxSamplesPerLaunch4 = 130560;
+constexpr int64_t kMaxSamplesDuo4 = 65472;
+constexpr int64_t kInt32Sums = 1LL << 31;
+static_assert(kMaxSamplesPerLaunch4 == 2 * 32 * ((kInt32Sums - 1) / 32896 / 32), "fused-product partial sums");
+static_assert((kMaxSamplesPerLaunch4 << 14) < kInt32Sums, "three-product sums");
+static_assert(((kMaxSamplesPerLaunch4 / 8 + 32) << 15) < kInt32Sums, "time-split sums");
+static_assert((kMaxSamplesDuo4 << 15) < kInt32Sums, "128-input segments' sums");
 
 constexpr int64_t kMaxSamplesPerLaunch8 = 133143;  // |re*re| <= 127^2 per sample
+static_assert(kMaxSamplesPerLaunch8 * 127 * 127 < kInt32Sums, "8+8-bit products");
 
 hipError_t launch_plain(int bits, const uint8_t *volts, int64_t T, int F, int N, int2 *acc,
                         int accumulate, hipStream_t s);
@@ -144,7 +156,6 @@ hipError_t launch_split4_blocks(int rb, const BlockTable &bt, int n_blocks, int 
 // 4+4-bit kernel for segments of 128 inputs, two work-groups per compute unit
 // (rows on 4-byte boundaries; with a block table, blocks of 64-sample chunks),
 // and the rule that takes it.
-constexpr int64_t kMaxSamplesDuo4 = 65472;   // int32 accumulators of 2^15 per sample
 bool duo4_taken(int N, int F, int64_t T, bool adds);   // adds: to running sums
 hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                        int accumulate, hipStream_t s);

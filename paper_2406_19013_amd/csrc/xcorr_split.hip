@@ -531,8 +531,13 @@ constexpr SplitCost kCost8H{0.0026, 0.006, 0.0072, 3.0, 4.5, 5.0, 9.5, 8.0, 0.00
 
 int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
 {
+    // Up to 256 samples of at most 64 inputs stay with the other kernel.  Measured
+    // (us, the other and this one): right for 33 to 64 inputs from 256 channels on
+    // (64 x 1024 x 256 11 and 18; 8+8-bit 21 and 20), but this one is the faster
+    // below that and for fewer inputs (16 x 8 x 256 5.2 and 3.7 from launch to
+    // launch, 32 x 4096 x 256 32 and 22; 8+8-bit 69 and 24).
     if (T <= 256 && pl.D <= 2 && pl.nseg == 1)
-        return 0;   // the smallest calls: the estimate itself would show
+        return 0;
     const double t = (double)T;
     auto regions = [&](int rb) {
         const double nseg = ((N + 31) / 32 + rb - 1) / rb;

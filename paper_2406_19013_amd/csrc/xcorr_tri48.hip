@@ -85,19 +85,6 @@ struct TsArgs {
 
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 
-template <int LOADS, int MAXR, int AFTER>
-__device__ __forceinline__ void ts_wait(int r)
-{
-    if constexpr (MAXR > 0) {
-        if (r >= MAXR)
-            wait_vmcnt<(LOADS * MAXR + AFTER < 63 ? LOADS * MAXR + AFTER : 63)>();
-        else
-            ts_wait<LOADS, MAXR - 1, AFTER>(r);
-    } else {
-        wait_vmcnt<(AFTER < 63 ? AFTER : 63)>();
-    }
-}
-
 template <int W, int ACC, int MB>
 __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const BlockTable &bt,
                                         const uint8_t *__restrict__ volts)
