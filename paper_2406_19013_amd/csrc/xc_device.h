@@ -18,16 +18,6 @@ typedef __attribute__((address_space(3))) v2i lds_v2i;
 
 constexpr int kThreads = 256;
 
-// Work-group b is dispatched to XCD b % 8.  Give each XCD a contiguous range
-// of work items so that the regions of one channel, and neighbouring channels
-// (adjacent bytes of every time row), share that XCD's L2.  The grid is a
-// multiple of 8; callers drop items >= the real count.
-__device__ __forceinline__ int xcd_item()
-{
-    const int per = (gridDim.x >> 3) * gridDim.y;
-    return (blockIdx.x & 7) * per + (int)blockIdx.y * (gridDim.x >> 3) + (blockIdx.x >> 3);
-}
-
 // A launch counts the threads of each grid dimension in 32 bits and drops the
 // rest without an error: a row of the grid is at most this many work-groups
 // (of up to 512 threads), and further ones go along y.
@@ -36,6 +26,16 @@ inline dim3 xcd_grid(int nitems)
 {
     const int groups = (nitems + 7) / 8 * 8, rows = (groups + kGridRow - 1) / kGridRow;
     return dim3(rows > 1 ? kGridRow : groups, rows);
+}
+
+// Work-group b is dispatched to XCD b % 8.  Give each XCD a contiguous range
+// of work items so that the regions of one channel, and neighbouring channels
+// (adjacent bytes of every time row), share that XCD's L2.  Returns nitems or
+// more for a work-group that has none.
+__device__ __forceinline__ int xcd_item(int nitems)
+{
+    const int b = (int)(blockIdx.y * kGridRow + blockIdx.x), per = (nitems + 7) >> 3;
+    return (b >> 3) < per ? (b & 7) * per + (b >> 3) : nitems;
 }
 
 // 16 consecutive bytes of one (t, f) row starting at input i0; zero outside

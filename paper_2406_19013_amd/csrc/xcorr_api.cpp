@@ -136,9 +136,9 @@ Choice choose(const xcorr_config &c, const xc::Plan &pl, Kernel4 k4, bool named,
             if (xc::gauss4_runs(pl, F, N)) {
                 if (const int rb = xc::split4_blocks(pl, F, N, T))
                     return {Launch::Split4, rb};
-                return {xc::duo4_taken(N, F, T, adds) ? Launch::Duo4
-                        : xc::tri48_taken(N, F, T)  ? Launch::Tri48
-                                                    : Launch::Gauss4};
+                return {xc::duo4_taken(N, F, T, adds)    ? Launch::Duo4
+                        : xc::tri48_taken(N, F, T, adds) ? Launch::Tri48
+                                                         : Launch::Gauss4};
             }
         } else if (xc::split4_unaligned(F, N, T)) {
             return {Launch::Split4, 1};

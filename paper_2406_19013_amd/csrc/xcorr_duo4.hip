@@ -145,8 +145,8 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     lds_u8 *const ring = (lds_u8 *)smem;
 
     const int xcd = blockIdx.x & 7, m = (int)(blockIdx.x >> 3), M = gridDim.x >> 3;
-    const int per = (a.nf * nreg + 7) / 8, first = xcd * per;   // this XCD's items (channel, region)
-    const int rlen = min(per, a.nf * nreg - first);
+    const int per = (a.nf * nreg + 7) / 8;   // this XCD's items (channel, region)
+    const int first = a.f0 * nreg + xcd * per, rlen = min(per, a.nf * nreg - xcd * per);
     const int n_my = rlen > m ? (rlen - m + M - 1) / M : 0;
     const int nch = (int)((a.T + C - 1) / C);
     const int total = n_my * nch;
@@ -175,9 +175,9 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     int is_k = 0, is_c = 0, issued = 0, islot = 0;
     int voff[LOADS];
     auto set_item = [&](int k) {
-        const int it = first + m + k * M, c = it / nreg, f = a.f0 + c;
+        const int it = first + m + k * M, f = it / nreg;
         int sa, sb;
-        segments(it - c * nreg, sa, sb);
+        segments(it - f * nreg, sa, sb);
         int ln = __lane_id();                 // recomputed per item: kept, these values would take
         asm volatile("" : "+v"(ln));          // the K loop's registers
 #pragma unroll
@@ -304,9 +304,9 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
     };
 
     auto epilogue = [&](int it) {
-        const int c = __builtin_amdgcn_readfirstlane(it / nreg), f = a.f0 + c;
+        const int f = __builtin_amdgcn_readfirstlane(it / nreg);
         int sa, sb;
-        segments(it - c * nreg, sa, sb);
+        segments(it - f * nreg, sa, sb);
         const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
         const int bytes = (int)(8 * P);
         // rows past input N - 1 lie past the end of the channel's triangle:

@@ -162,7 +162,7 @@ hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, in
 
 // 4+4-bit kernel for one triangle of 129 to 192 inputs, as four segments of
 // 48 (same operands), and its rule.
-bool tri48_taken(int N, int F, int64_t T);
+bool tri48_taken(int N, int F, int64_t T, bool adds);
 hipError_t launch_tri48(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                         int accumulate, hipStream_t s);
 

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(kThreads) void xc_plain_kernel(
     constexpr int PIECES = 2 * KC * SEG / 16;   // 16-byte pieces per chunk (rows + cols)
     __shared__ __attribute__((aligned(16))) uint8_t sm[2][KC][SEG];
 
-    const int item = xcd_item();
+    const int item = xcd_item(nitems);
     if (item >= nitems)
         return;
     const int f = item / ntiles;

@@ -20,7 +20,7 @@ void xc_mfma4_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N,
     constexpr int NBUF = mfma4_nbuf(D, KC);
     __shared__ __attribute__((aligned(1024))) uint8_t smem[mfma4_smem_bytes(D, KC)];
 
-    const int item = xcd_item();
+    const int item = xcd_item(nitems);
     if (item >= nitems)
         return;
     const int f = item / R;

@@ -21,7 +21,7 @@ void xc_mfma4f_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N
     constexpr int NBUF = fused_nbuf(D);
     __shared__ __attribute__((aligned(1024))) uint8_t smem[fused_smem_bytes(D)];
 
-    const int item = xcd_item();
+    const int item = xcd_item(nitems);
     if (item >= nitems)
         return;
     const int f = item / R;
@@ -54,7 +54,7 @@ void xc_mfma4f_blocks_kernel(const BlockTable bt, int64_t T, int F, int N, int n
     constexpr int NBUF = fused_nbuf(D);
     __shared__ __attribute__((aligned(1024))) uint8_t smem[fused_smem_bytes(D)];
 
-    const int item = xcd_item();
+    const int item = xcd_item(nitems);
     if (item >= nitems)
         return;
     const int f = item / R;

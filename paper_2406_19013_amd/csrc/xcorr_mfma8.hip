@@ -517,7 +517,7 @@ void xc_mfma8_kernel(const uint8_t *__restrict__ volts, int64_t T, int F, int N,
     __shared__ __attribute__((aligned(1024))) uint8_t smem[mfma8_smem_bytes(KC, D)];
     static_assert(4 * mfma8_epilogue_tiles(D) * 4096 + 2 * D * 64 * 4 <= mfma8_smem_bytes(KC, D), "stage fits");
 
-    const int item = xcd_item();
+    const int item = xcd_item(nitems);
     if (item >= nitems)
         return;
     const int f = item / R;

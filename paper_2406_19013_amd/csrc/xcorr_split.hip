@@ -453,7 +453,7 @@ __global__ __launch_bounds__(kSpThreads) __attribute__((amdgpu_waves_per_eu(RB =
 void xc_split_kernel(const uint8_t *__restrict__ volts, const SpArgs a, const BlockTable bt)
 {
     __shared__ __attribute__((aligned(1024))) uint8_t smem[sp_smem_bytes(RB)];
-    const int item = xcd_item();
+    const int item = xcd_item(a.items);
     if (item >= a.items)
         return;
     const int f = item / a.nreg, r = item - f * a.nreg;
@@ -558,7 +558,7 @@ int split_choice(const SplitCost &c, const Plan &pl, int F, int N, int64_t T)
         other = 4.5 + t * std::max(0.0068, 0.0168 * tri / 512.0) + 0.0132 * tri;
         if (rect > 0)
             other += 5.7 + t * std::max(0.0115, 0.0185 * rect / 512.0) + 0.026 * rect;
-    } else if (c.four_bit && tri48_taken(N, F, T)) {
+    } else if (c.four_bit && tri48_taken(N, F, T, true)) {
         other = std::ceil(F / 256.0) * (6.0 + 0.0105 * t);
     } else if (c.one_launch && pl.nseg > 1)
         other = std::ceil((tri_items + rect_items) / 256.0) * (c.rect_fixed + c.rect_chunk * t);

@@ -324,7 +324,7 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
     }
     wait_vmcnt_chunks<kTsLoads, kTsRing - 1>(kTsRing - 1);
     barrier_no_fence();
-    // operands of the stream's first step
+    // operands of a channel's first step
     auto begin = [&](lds_u8 *p) {
         if constexpr (TRI) {
             static_for<0, 6>([&](auto k) { read(p, k); });
@@ -361,8 +361,8 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
             issue_open();
         };
         // A step of 64 samples.  Half blocks are unpacked in place once their
-        // last product of a step is issued (past a channel's end what is read
-        // and unpacked ahead is the next one's).
+        // last product of a step is issued (past a channel's or the stream's
+        // end what is read and unpacked ahead is not used).
         static_for<0, 2>([&](auto s) {
             lds_u8 *const qn = s ? pn : p + 64 * kTsRow;
             if constexpr (TRI) {
@@ -428,6 +428,7 @@ __device__ __forceinline__ void ts_wave(uint8_t *smem, const TsArgs &a, const Bl
             stored_after = issued;
             ++ck;
             clear();
+            begin(pn);   // (kept across the epilogue instead: 256 -> 257 us at 192 x 1024 x 4096)
         }
     }
 }
@@ -456,9 +457,13 @@ void xc_tri48_kernel(const uint8_t *__restrict__ volts, const TsArgs a, const Bl
 // 28 and 30; 192 x 256 x 1024 26.6 and 26.2.  Below 129 inputs the triangles of
 // up to four blocks are smaller than its padding; above 192 it has no regions.
 // A launch of at most half a slot leaves it behind the three-product kernel
-// (192 x 1024 x 64 34.2 and 30.8, x 128 35.0 and 34.1; 160 x 512 x 64 17.1 and
-// 15.2) until the results are what takes the time (192 x 4096 x 64 176 and 180).
-bool tri48_taken(int N, int F, int64_t T) { return N > 128 && N <= 192 && (T > 64 || F > 2048); }
+// (192 x 1024 x 64 34.6 and 30.8, x 128 35.7 and 34.1; 160 x 512 x 64 17.3 and
+// 15.2; 176 x 4096 x 32 143 and 138), except where it adds to the running sums of
+// many channels (144 x 4096 x 64 295 and 310, 192 x 4096 x 32 487 and 498).
+bool tri48_taken(int N, int F, int64_t T, bool adds)
+{
+    return N > 128 && N <= 192 && (T > 64 || (adds && F > 2048));
+}
 
 hipError_t launch_tri48(const uint8_t *volts, const BlockTable *bt, int64_t T, int F, int N, int2 *out, const int2 *in,
                         int accumulate, hipStream_t s)
