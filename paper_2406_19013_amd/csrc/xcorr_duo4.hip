@@ -517,15 +517,16 @@ void xc_duo4_kernel(const uint8_t *__restrict__ volts, const DuoArgs a, const Bl
 // three-product kernel (us): 100 inputs x 256 channels x 2048 samples 20 and
 // 34; 128 x 512 x 4096 69 and 71; 200 x 16 x 2048 47 and 60; 2048 x 8 x 512 49
 // and 61; 300 x 512 x 64 46 and 51; 128 x 1024 x 64 16.2 and 17.0.  With 96 inputs a
-// quarter of the triangle would be padding.  One triangle of many channels and a
-// few samples is all epilogue, which the other kernel has the shorter of where
-// nothing is added to running sums: 112 x 4096 x 64 48.4 and 41.5 (adding 170 and
-// 179), 128 x 4096 x 32 53.1 and 51.3.
+// quarter of the triangle would be padding.  One triangle of up to 112 inputs,
+// many channels and a few samples is all epilogue, which the other kernel has
+// the shorter of where nothing is added to running sums (112 x 4096 x 64 48.4 and
+// 41.5, adding 170 and 179; 128 x 4096 x 32 53.1 and 51.3, but 234 and 239 with a
+// second launch that adds to it).
 bool duo4_taken(int N, int F, int64_t T, bool adds)
 {
     if (T > kMaxSamplesDuo4)
         return false;
-    return N > 192 || (N > 96 && N <= 128 && (adds || T > 64 || F <= 2048));
+    return N > 192 || (N > 96 && N <= 128 && (adds || N > 112 || T > 64 || F <= 2048));
 }
 
 // A launch of more than about 2 ms goes as two, each over half of the channels:

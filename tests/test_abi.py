@@ -240,7 +240,8 @@ def test_ingest_kernel_follows_size_and_alignment(monkeypatch):
     assert kernel(192, 32, 4096) == "xc_split_kernel"                # few channels
     assert kernel(192, 1024, 65) == kernel(132, 4096, 128) == "xc_tri48_kernel"
     assert kernel(192, 1024, 64) == kernel(132, 4096, 64) == "xc_gauss4_kernel"      # at most half a slot
-    assert kernel(112, 4096, 64) == "xc_gauss4_kernel" and kernel(112, 4096, 65) == kernel(112, 2048, 64) == "xc_duo4_kernel"
+    assert kernel(112, 4096, 64) == "xc_gauss4_kernel" and kernel(112, 4096, 65) == "xc_duo4_kernel"
+    assert kernel(112, 2048, 64) == kernel(128, 4096, 64) == "xc_duo4_kernel"
     assert kernel(128, 512, 4096) == kernel(512, 512, 2048) == kernel(100, 512, 1000) == "xc_duo4_kernel"
     assert kernel(512, 512, 65_473) == "xc_gauss4_kernel"            # past duo4's int32 bound
     assert kernel(96, 2048, 1024) == kernel(64, 4096, 2048) == "xc_gauss4_kernel"
