@@ -23,10 +23,10 @@
 // What bounds it: for a triangle the stream (128 inputs x 2048 channels x 4096
 // samples, 1.2 GB: 292 -> 260 us, 4.7 TB/s); for rectangles the power that the
 // products draw, then each segment's samples being read once per pair of
-// segments.  Against the three-product kernel: 512 inputs x 512 channels x 2048
-// samples 570 -> 481 us; 256 x 512 x 2048 162 -> 136; 200 x 512 x 2000 152 ->
-// 125; 1024 x 64 x 2048 267 -> 228; 128 x 256 x 4096 60 -> 37 (that kernel
-// takes channels in pairs, which leaves half the chip idle).
+// segments.  Against the three-product kernel, in one run: 512 inputs x 512
+// channels x 2048 samples 556 -> 474 us; 256 x 512 x 2048 158 -> 136; 1024 x 64 x
+// 2048 277 -> 224; and 200 x 512 x 2000 152 -> 125; 128 x 256 x 4096 60 -> 37 (that
+// kernel takes channels in pairs, which leaves half the chip idle).
 #include "xc_mfma4.h"
 
 #include <algorithm>
@@ -489,7 +489,7 @@ __device__ __forceinline__ void duo_roles(uint8_t *smem, const DuoArgs &a, const
 // first half of an XCD's work-groups the triangles first, the second half, which
 // joins them on the compute units, the rectangles first: the triangles' stream
 // and the rectangles' products then share the chip.  One launch for each shape
-// took 500 us at 512 inputs x 512 channels x 2048 samples, this 486; 256 x 512 x
+// took 500 us at 512 inputs x 512 channels x 2048 samples, this 486 beside it; 256 x 512 x
 // 2048 150 and 137; 384 x 64 x 1024 35 and 32.
 template <int ACC, int MB>
 __global__ __launch_bounds__(kDuoThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
