@@ -108,7 +108,7 @@ constexpr DuoProduct duo_product(int SH, int ROLE, int k)
 struct DuoArgs {
     int64_t T;        // samples (MB = 1: whole blocks)
     int F, N;
-    int f0, nf;       // channels of this launch
+    int nf, lead;     // channels of this launch; bytes of a time row before them
     int ntri, nrect;  // triangles and rectangles per channel
     int2 *out;        // [F][P] results
     const int2 *in;   // [F][P] running sums (ACC = 1)
@@ -146,7 +146,7 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
 
     const int xcd = blockIdx.x & 7, m = (int)(blockIdx.x >> 3), M = gridDim.x >> 3;
     const int per = (a.nf * nreg + 7) / 8;   // this XCD's items (channel, region)
-    const int first = a.f0 * nreg + xcd * per, rlen = min(per, a.nf * nreg - xcd * per);
+    const int first = xcd * per, rlen = min(per, a.nf * nreg - first);
     const int n_my = rlen > m ? (rlen - m + M - 1) / M : 0;
     const int nch = (int)((a.T + C - 1) / C);
     const int total = n_my * nch;
@@ -204,7 +204,7 @@ __device__ __forceinline__ void duo_wave(uint8_t *smem, const DuoArgs &a, const 
             src = volts + (rows > 0 ? row * row_bytes : 0);
         }
         __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)src, (short)0, (int)(rows * row_bytes), 0x00020000);
+            __builtin_amdgcn_make_buffer_rsrc((void *)src, (short)0, rows > 0 ? (int)(rows * row_bytes) - a.lead : 0, 0x00020000);
         lds_u8 *dst = ring + islot * SLOT + wave * LOADS * 1024;
 #pragma unroll
         for (int k = 0; k < LOADS; ++k)
@@ -556,10 +556,11 @@ hipError_t launch_duo4(const uint8_t *volts, const BlockTable *bt, int64_t T, in
     const int launches = duo4_launches(T, F, nseg + pairs);
     for (int k = 0; k < launches; ++k) {
         const int f0 = (int)((int64_t)F * k / launches), nf = (int)((int64_t)F * (k + 1) / launches) - f0;
-        const DuoArgs a{T, F, N, f0, nf, nseg, pairs, out, in};
+        const int64_t P = (int64_t)N * (N + 1) / 2;
+        const DuoArgs a{T, F, N, nf, f0 * N, nseg, pairs, out + f0 * P, in + f0 * P};
         const int per = (int)(((int64_t)nf * std::max(nseg, pairs) + 7) / 8);
         const int grid = 8 * std::max(1, std::min(compute_units() / 4, per));   // two per compute unit
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts, a, table);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kDuoThreads), 0, s, volts + (int64_t)f0 * N, a, table);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;

@@ -25,7 +25,7 @@
 // stood at them for 400 of 3700 cycles); a ring of 4 slots is faster than one
 // of 6 (45.1 -> 43.4 us at 192 x 512 x 1024).
 //
-// Against the three-product kernel on blocks of 32, in one run (boxes differ by
+// Against the three-product kernel on blocks of 32, in one run (cards differ by
 // some 5 %): 192 inputs x 1024 channels x 4096 samples 266 -> 250 us (3.8 TB/s);
 // 160 x 1024 x 2048 136 -> 127; 192 x 512 x 1024 44.7 -> 42.7; 192 x 4096 x 1024
 // 372 -> 367.
