@@ -188,8 +188,9 @@ int xcorr_destroy(xcorr_ctx *ctx);
  * Section 2.3 runs once per array; a batch correlates up to XCORR_MAX_BATCH
  * arrays of uneven N, F and sample count in one kernel launch (a member that
  * fills the chip with a kernel for its size gets a launch of its own ahead of
- * it, on the same stream, unless its tile is named by its config or tuned).  Where every array of that launch has N a multiple
- * of 16 and a 16-byte-aligned input, each array's region shapes are jobs of the
+ * it, on the same stream, unless its tile is named by its config or tuned).
+ * Where every array of that launch has N a multiple of 16 and a
+ * 16-byte-aligned input, each array's region shapes are jobs of the
  * three-product kernel that every work-group walks in turn; otherwise one
  * kernel drains a work queue of (array, channel, region) items.  Results, the
  * integration bookkeeping and the dumps stay per context (xcorr_dump).
@@ -241,10 +242,10 @@ int xcorr_batch_destroy(xcorr_batch *b);
  * its size, also among kernels that take no tile and are often faster than
  * every tile: xcorr_ingest_kernel (pure host) names the one that the first
  * launch of an integration, xcorr_ingest(d_volts, n_samples), runs in a context
- * of this config (d_volts counts by its alignment only).  xcorr_plan_tile (pure host) reports
- * the tile xcorr_init (batch = 0) or xcorr_batch_init (batch = 1) would use
- * and whether it came from the cache.  The tuners block until their timing
- * runs on `stream` have finished.  xcorr_autotune_query gives the scratch
+ * of this config (d_volts counts by its alignment only).  xcorr_plan_tile (pure
+ * host) reports the tile xcorr_init (batch = 0) or xcorr_batch_init (batch = 1)
+ * would use and whether it came from the cache.  The tuners block until their
+ * timing runs on `stream` have finished.  xcorr_autotune_query gives the scratch
  * size (accumulators + input block + queue counters).
  * Errors: as xcorr_query, XCORR_E_INVAL for the plain path, a NULL output,
  * or (batch) a config that is not 4+4-bit int8 MFMA; XCORR_E_NOMEM for
@@ -401,8 +402,8 @@ int xcorr_reorder_destroy(xcorr_reorder *r);
  * (F*P*2*4 bytes, rounded up to 256) exceed it are refused with
  * XCORR_E_NOMEM before anything is enqueued.  The first launch of an
  * integration overwrites the array, so nothing needs clearing; it keeps the
- * contents of the last call that used it.  Calls that overlap on one GPU (two streams, or two
- * host threads) share the array and race.  Errors: as xcorr_query and
+ * contents of the last call that used it.  Calls that overlap on one GPU (two
+ * streams, or two host threads) share the array and race.  Errors: as xcorr_query and
  * xcorr_ingest_dump, XCORR_E_NOMEM as above, XCORR_E_HIP if the array's
  * address cannot be looked up.
  */
